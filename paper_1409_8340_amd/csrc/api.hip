@@ -1863,7 +1863,6 @@ tdgl_status tdgl_set_mu(tdgl_ctx *ctx, int inst, const float *mu) {
     if (!ctx->inst[inst].p.driven) return fail(TDGL_ESTATE, "instance %d is not driven: mu is identically 0", inst);
     hipLaunchKernelGGL(k_mu_io, dim3(fill_grid(ctx->inst[inst].d.N)), dim3(256), 0, ctx->stream, ctx->d_inst,
                        inst, (float *)mu, 0);
-    hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 10, 0.0);
     LAUNCHCHK();
     return TDGL_OK;
 }
@@ -1904,10 +1903,8 @@ tdgl_status tdgl_set_scalars(tdgl_ctx *ctx, int inst, const tdgl_scalars *sc) {
     if (s) return s;
     if (!sc) return fail(TDGL_EINVAL, "null scalars");
     if (!ctx->inst[inst].p.driven && sc->K != 0.0) return fail(TDGL_EINVAL, "undriven instance: K must be 0");
-    const double v[7] = {sc->K, sc->t, sc->V_sum, (double)sc->n, (double)sc->n_avg, sc->E_last, sc->J_av_last};
-    for (int f = 0; f < 7; ++f)
-        hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, f, v[f]);
-    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, ctx->stream, ctx->d_inst + inst, 1, (const double *)nullptr);
+    const StateScalars v{sc->K, sc->t, sc->V_sum, (double)sc->n, (double)sc->n_avg, sc->E_last, sc->J_av_last};
+    hipLaunchKernelGGL(k_scalars_set, dim3(1), dim3(256), 0, ctx->stream, ctx->d_inst, inst, v);
     LAUNCHCHK();
     return TDGL_OK;
 }
@@ -1915,8 +1912,7 @@ tdgl_status tdgl_set_scalars(tdgl_ctx *ctx, int inst, const tdgl_scalars *sc) {
 tdgl_status tdgl_voltage_window_reset(tdgl_ctx *ctx, int inst) {
     tdgl_status s = check_ctx(ctx, inst);
     if (s) return s;
-    hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 2, 0.0);
-    hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 4, 0.0);
+    hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 15, 0.0);
     LAUNCHCHK();
     return TDGL_OK;
 }

@@ -82,20 +82,28 @@ __global__ void k_links(const Inst *__restrict__ insts, int which, const double 
 __global__ __launch_bounds__(FIN_THREADS) void k_solve_finalize(const Inst *__restrict__ insts, int ninst,
                                                                   int count_step, int nl, int fused,
                                                                   unsigned long long *pub, unsigned seq) {
-    // one work-group per instance: the first wavefront scans the rows, then
-    // all threads clear them.  pub (host-driven solves): the iteration count
+    // one work-group per instance: its half-wavefronts read the launched rows
+    // side by side (one after the other they cost a memory round trip per
+    // sweep, 7-11 us a solve), one thread finds the first converged one and
+    // all threads clear the rows that the solve can have written.  pub (host-driven solves): the iteration count
     // and the last tested residual go to the host at pub[ii] and
     // pub[ninst + ii], tagged seq.
     const int ii = blockIdx.x;
     if (ii >= ninst) return;
     const Inst &I = insts[ii];
     DevState *st = I.st;
+    __shared__ float rows[kMaxIter];
+    const int cap = min(I.max_iter, nl);
+    for (int l = threadIdx.x / NSLOT; l < cap; l += FIN_THREADS / NSLOT) {
+        const float v = row_max_half(I.res, I.rstride, l);
+        if ((threadIdx.x & (NSLOT - 1)) == 0) rows[l] = v;
+    }
+    __syncthreads();
     if (threadIdx.x < 64) {
-        const int cap = min(I.max_iter, nl);
         int sweeps = cap, capped = 1;
         float last = 0.f;
         for (int l = 0; l < cap; ++l) {
-            last = row_max_wave(I.res, I.rstride, l);
+            last = rows[l];
             if (last < I.tol) { sweeps = l + 1; capped = 0; break; }
         }
         if (threadIdx.x == 0) {
@@ -135,9 +143,9 @@ __global__ __launch_bounds__(FIN_THREADS) void k_solve_finalize(const Inst *__re
             }
         }
     }
-    __syncthreads();
-    // clear the words for the next step
-    const int words = I.max_iter * NSLOT;
+    // clear the words for the next step (a pair that starts at sweep nl - 1
+    // writes row nl too; none goes further)
+    const int words = min(I.max_iter, nl + 1) * NSLOT;
     for (int w = threadIdx.x; w < words; w += FIN_THREADS) I.res[(size_t)w * I.rstride] = 0u;
 }
 
@@ -345,6 +353,28 @@ __global__ void k_fill_u(unsigned *p, long n, unsigned v) {
         p[i] = v;
 }
 
+// The scalars of an exact resume and the x links at the new K (the table of
+// k_links), as one work-group.
+__global__ __launch_bounds__(256) void k_scalars_set(const Inst *__restrict__ insts, int inst, StateScalars v) {
+    const Inst &I = insts[inst];
+    DevState *st = I.st;
+    const double K = I.driven ? v.K : 0.0, Bz = st->Bz;
+    const double yref = link_yref(I, st);
+    if (threadIdx.x == 0) {
+        st->K = v.K;
+        st->t = v.t;
+        st->V_sum = v.V_sum;
+        st->n = v.n;
+        st->n_avg = v.n_avg;
+        st->E_last = v.E_last;
+        st->J_last = v.J_last;
+    }
+    for (int j = threadIdx.x; j < I.ny; j += blockDim.x) {
+        const double yb = j * I.hy - yref;
+        I.ux[j] = expi(I.hx * (K + Bz * yb));
+    }
+}
+
 // psi in/out through the current buffer index (known only on the device).
 __global__ void k_psi_io(const Inst *__restrict__ insts, int inst, float2 *ext, int to_ext) {
     const Inst &I = insts[inst];
@@ -359,6 +389,7 @@ __global__ void k_psi_io(const Inst *__restrict__ insts, int inst, float2 *ext, 
 __global__ void k_mu_io(const Inst *__restrict__ insts, int inst, float *ext, int to_ext) {
     const Inst &I = insts[inst];
     const float mean = (float)I.st->mu_mean;
+    if (!to_ext && blockIdx.x == 0 && threadIdx.x == 0) I.st->mu_mean = 0.0;
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < I.N; i += (long)gridDim.x * blockDim.x) {
         if (to_ext) ext[i] = I.mu[i] - mean;
         else I.mu[i] = ext[i];
@@ -398,6 +429,7 @@ __global__ void k_state_set(const Inst *__restrict__ insts, int inst, int field,
         case 12: st->cur = (int)v; break;
         case 13: st->By = v; break;
         case 14: st->yz = (int)v; break;
+        case 15: st->V_sum = st->n_avg = v; break;
         default: break;
     }
 }

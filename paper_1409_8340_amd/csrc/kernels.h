@@ -38,6 +38,7 @@ __global__ void k_psi2_partial(const Inst *insts, const int *prefix, int ninst);
 __global__ void k_fill_c(float2 *p, long n, float re, float im);
 __global__ void k_fill_f(float *p, long n, float v);
 __global__ void k_fill_u(unsigned *p, long n, unsigned v);
+__global__ void k_scalars_set(const Inst *insts, int inst, StateScalars v);
 __global__ void k_psi_io(const Inst *insts, int inst, float2 *ext, int to_ext);
 __global__ void k_mu_io(const Inst *insts, int inst, float *ext, int to_ext);
 __global__ void k_state_set(const Inst *insts, int inst, int field, double v);

@@ -64,6 +64,11 @@ struct DevState {
     int pad4;
 };
 
+// The scalars that tdgl_set_scalars restores.
+struct StateScalars {
+    double K, t, V_sum, n, n_avg, E_last, J_last;
+};
+
 // Scalars of the adjoint sweep over one step (device resident).
 struct AdjState {
     double Kbar;   // adjoint of K, accumulated backwards through the steps
@@ -263,14 +268,20 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 }
 
 // Instance owning logical block `b` of a batched launch (prefix has ninst+1
-// entries; instance i owns [prefix[i], prefix[i+1])).
+// entries; instance i owns [prefix[i], prefix[i+1])): the last i with
+// prefix[i] <= b.  Every wavefront compares 64 entries at once, one load
+// instead of the log2(ninst) dependent loads of a bisection, which every
+// work-group of a batch paid before its first useful load.  All 64 lanes must
+// be active.
 __device__ __forceinline__ int find_inst(const int *__restrict__ prefix, int ninst, int b) {
-    int lo = 0, hi = ninst - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= b) lo = mid; else hi = mid - 1;
+    if (ninst == 1) return 0;
+    const int lane = (int)(threadIdx.x & 63);
+    for (int base = 0;; base += 64) {
+        const int i = base + lane;
+        const bool le = i < ninst && prefix[i] <= b;
+        const int c = (int)__popcll(__ballot(le));
+        if (c < 64 || base + 64 >= ninst) return base + c - 1;
     }
-    return lo;
 }
 
 // Convergence rows: slot word for an atomic update and the row maximum.
@@ -280,20 +291,24 @@ __device__ __forceinline__ unsigned *row_slot(unsigned *base, int rstride, int r
 // The words are read with device-scope atomic loads: in a persistent
 // kernel they were written by other work-groups' atomics since this
 // work-group last looked, and no cached copy may answer.  The whole
-// wavefront reads a row at once: lane s loads slot s mod NSLOT, a butterfly
-// over each half-wave combines them, and every lane returns the row
-// maximum.  All 64 lanes must be active.
-__device__ __forceinline__ float row_max_wave(const unsigned *base, int rstride, int row) {
+// half-wavefront reads a row at once: lane s loads slot s mod NSLOT and a
+// butterfly over the half combines them; the two halves may read different
+// rows (row_max_half) or the same one (row_max_wave: every lane returns the
+// row maximum).  All lanes of the half must be active.
+__device__ __forceinline__ float row_max_half(const unsigned *base, int rstride, int row) {
     static_assert(NSLOT == 32, "one slot per lane of a half-wave");
     const int s = (int)(threadIdx.x & (NSLOT - 1));
     unsigned m = __hip_atomic_load(base + ((size_t)row * NSLOT + s) * rstride, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int o = NSLOT / 2; o >= 1; o >>= 1) {
-        const unsigned v = (unsigned)__shfl_xor((int)m, o, 64);
+        const unsigned v = (unsigned)__shfl_xor((int)m, o, NSLOT);
         m = v > m ? v : m;
     }
     return __uint_as_float(m);
+}
+__device__ __forceinline__ float row_max_wave(const unsigned *base, int rstride, int row) {
+    return row_max_half(base, rstride, row);
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror and Shaw, SC'11): ten rounds, each
