@@ -116,7 +116,9 @@ typedef struct tdgl_step_stats {
                                pairs start at the second iterate and
                                (sweeps + 1) / 2 when one single sweep comes
                                first; launches that exit at once and
-                               corrective sweeps excluded */
+                               corrective sweeps excluded (block solves of
+                               small grids, see tdgl_tiling, count as single
+                               sweeps) */
     int single_first_steps; /* steps whose two-sweep solve began with one
                                single sweep, so that the pairs end on even
                                iterates (chosen when the recent sweep
@@ -366,7 +368,11 @@ tdgl_status tdgl_step_graph(tdgl_ctx *ctx, int nsteps, int budget, tdgl_step_sta
 tdgl_status tdgl_poisson_solve(tdgl_ctx *ctx, const float *f, float *mu);
 
 /* Stencil tiling: work-groups of 64 x 4*rows grid columns marching through
- * z runs of `chunk` planes. */
+ * z runs of `chunk` planes.  Contexts of up to 2^20 nodes, and films (nz = 1,
+ * open z) of any size, make two (films: four) Jacobi iterates per launch from
+ * blocks of the grid held on chip when the tiling asks for single sweeps
+ * (fused = persistent = 0); rows and chunk then concern the other passes.
+ * The results are the same bits. */
 typedef struct tdgl_tiling {
     int rows;        /* rows of the tile per thread: 1, 2 or 4               */
     int chunk;       /* z planes per work-group (instance 0 for tdgl_autotune) */
@@ -406,7 +412,7 @@ typedef struct tdgl_tiling {
  * super-tile height (super_rows 16 or 32) and keep
  * the stencil chunk of the fastest single sweep with the same rows and
  * hints) on the context's stream and keeping the fastest per iteration;
- * then 16 sweeps of
+ * the block launch of small grids is timed against it; then 16 sweeps of
  * that tiling in one persistent launch are timed, and persistent solves are
  * chosen when they are at least 10 % faster per sweep.  The timing sweeps
  * read the current psi~ and b/M, (ht/2)/M arrays and write only the spare

@@ -462,6 +462,12 @@ struct tdgl_ctx {
     int *d_pref_sr = nullptr;  // ... and of the seam-ring pre-pass (seam2 instances)
     int *d_pref_r4 = nullptr;  // blocks of the four-row Poisson right-side pass
     int tot_b = 0, tot_i = 0, tot_sr = 0, tot_r4 = 0;
+    // block solves (k_blk): the shape's index in kBlkShapes for a context of
+    // this size (-1: too large), whether the tiling uses it, and the
+    // assemble's iterates in the current solve
+    int *d_pref_blk = nullptr;
+    int tot_blk = 0, blk_shape = -1, blk_a = 1;
+    bool blk = false, blk_on = true;  // blk_on: the tiling does not rule them out
     int rhs_rows = 0;  // rows per thread of the Poisson right side (0: rows)
     int *d_np_st = nullptr, *d_np_flat = nullptr, *d_np_mg0 = nullptr;
     int *d_np_r4 = nullptr;  // per instance: blocks of the four-row right-side pass
@@ -557,6 +563,7 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
     int *pref_i = cv.take<int>(n + 1);
     int *pref_sr = cv.take<int>(n + 1);
     int *pref_r4 = cv.take<int>(n + 1);
+    int *pref_blk = cv.take<int>(n + 1);
     int *np_st = cv.take<int>(n);
     int *np_r4 = cv.take<int>(n);
     int *np_flat = cv.take<int>(n);
@@ -730,6 +737,7 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
         ctx->d_pref_i = pref_i;
         ctx->d_pref_sr = pref_sr;
         ctx->d_pref_r4 = pref_r4;
+        ctx->d_pref_blk = pref_blk;
         ctx->d_np_st = np_st;
         ctx->d_np_r4 = np_r4;
         ctx->d_np_flat = np_flat;
@@ -756,6 +764,39 @@ tdgl_status check_ctx(tdgl_ctx *ctx, int inst) {
 }
 
 int fill_grid(long n) { return (int)std::min<long>(std::max<long>(cdiv(n, 256), 1), 8192); }
+
+// Block shapes of k_blk and the one a context takes (-1: none).  Measured per
+// iteration in back-to-back launches, single sweeps first: 32 x 32 x 16
+// 5.0 -> 2.5 us and 72 x 60 x 10 5.2 -> 2.5 us on small blocks (3.4 us on
+// 32 x 8 x 4: too few for the chip); 64 x 64 x 64 5.3 -> 3.6 us (3.95 on
+// 16 x 8 x 2) and 128 x 128 x 32 6.0 -> 4.7 us (5.6); 300 x 180 x 50 18.8 ->
+// 19.8 us: there the halo's iterates cost more than the launches they save.
+// Films make four iterates a launch: 512 x 512 x 1 4.5 -> 1.8 us (2.5 us with
+// three, 2.8 with two), and their halo has no planes to recompute, so they
+// take blocks at any size.  tdgl_autotune measures the block launch against
+// the best other tiling.
+struct BlkShape {
+    int bx, by, bz, S, hz;
+};
+#define TDGL_BLK_ROW(BX, BY, BZ, S, HZ) {BX, BY, BZ, S, HZ},
+constexpr BlkShape kBlkShapes[] = {TDGL_BLK_VARIANTS(TDGL_BLK_ROW)};
+#undef TDGL_BLK_ROW
+constexpr long long kBlkSmallNodes = 128ll << 10, kBlkNodes = 1ll << 20;
+int blk_shape_for(const std::vector<InstHost> &inst) {
+    long long nodes = 0;
+    bool film = true;
+    for (const auto &h : inst) {
+        nodes += h.d.N;
+        film = film && h.p.nz == 1 && h.p.bc[2] == TDGL_OPEN;
+    }
+    if (film) return 2;
+    return nodes <= kBlkSmallNodes ? 0 : (nodes <= kBlkNodes ? 1 : -1);
+}
+int blk_depth(const tdgl_ctx *c) { return kBlkShapes[c->blk_shape].S; }
+
+// Whether this context's Jacobi solves run as block launches: a single-sweep
+// tiling on a grid small enough, and no z-seam phase (which k_blk has not).
+void update_blk(tdgl_ctx *c) { c->blk = c->blk_on && c->blk_shape >= 0 && !c->fused && !c->persist && !c->any_zseam; }
 
 tdgl_status upload_tables(tdgl_ctx *ctx) {
     for (int i = 0; i < ctx->n; ++i) {
@@ -838,6 +879,20 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         } else if (h.p.driven) {
             ctx->any_mg = true;
         }
+    }
+    {
+        ctx->blk_shape = blk_shape_for(ctx->inst);
+        if (ctx->blk_shape >= 0) {
+            const BlkShape b = kBlkShapes[ctx->blk_shape];
+            std::vector<int> pb(n + 1, 0);
+            for (int i = 0; i < n; ++i) {
+                const tdgl_params &p = ctx->inst[i].p;
+                pb[i + 1] = pb[i] + cdiv(p.nx, b.bx) * cdiv(p.ny, b.by) * cdiv(p.nz, b.bz);
+            }
+            HIPCHK(hipMemcpy(ctx->d_pref_blk, pb.data(), (n + 1) * 4, hipMemcpyHostToDevice));
+            ctx->tot_blk = pb[n];
+        }
+        update_blk(ctx);
     }
     ctx->tot_st = ps[n];
     ctx->tot_flat = pf[n];
@@ -1039,8 +1094,30 @@ void launch_rhs(tdgl_ctx *c) {
 // Per-instance counts of the partial sums the right-side pass writes.
 const int *rhs_parts(const tdgl_ctx *c) { return c->rhs_rows == 4 ? c->d_np_r4 : c->d_np_st; }
 
+// One launch of a block solve: ns iterates from psi^(l) as launch number
+// `pass`, after a launch of np iterates (MODE_SWEEP; l = -1 timing, l = -2
+// the corrective launch), or the assemble with the first ns iterates.
+template <int MODE>
+void launch_blk(tdgl_ctx *c, int l, int ns, int np, int pass) {
+    unsigned long long *pub = (MODE == MODE_SWEEP && c->pub_on && l > 0) ? c->d_pub : nullptr;
+    int k = 0;
+#define TDGL_BLK_LAUNCH(BX, BY, BZ, S, HZ)                                                                            \
+    if (c->blk_shape == k++) {                                                                                    \
+        const auto fn = c->any_yz ? k_blk<BX, BY, BZ, S, HZ, MODE, true> : k_blk<BX, BY, BZ, S, HZ, MODE, false>;       \
+        hipLaunchKernelGGL(fn, dim3(c->tot_blk), dim3(blk_threads(BX, BY, S)), 0, c->stream, c->d_inst,           \
+                           c->d_pref_blk, c->n, l, ns, np, pass, pub, c->pub_seq);                                \
+    }
+    TDGL_BLK_VARIANTS(TDGL_BLK_LAUNCH)
+#undef TDGL_BLK_LAUNCH
+}
+
 // The assemble pass, with the Langevin draws where some instance has them.
 void launch_assemble(tdgl_ctx *c, int l = 0) {
+    if (c->blk) {
+        if (c->noisy) launch_blk<MODE_FIRSTN>(c, l, c->blk_a, 0, 0);
+        else launch_blk<MODE_FIRST>(c, l, c->blk_a, 0, 0);
+        return;
+    }
     if (c->noisy)
         launch_stencil<MODE_FIRSTN>(c, l);
     else
@@ -1158,6 +1235,31 @@ int pick_schedule(tdgl_ctx *ctx, int kind) {
     return c2 < c1 ? 2 : 1;
 }
 
+// Iterates the assemble of a block solve makes (1 .. S) so that solves of the
+// recent sweep counts end on a launch's last iterate with the fewest
+// launches, corrective ones included (S without history).
+int pick_blk_a(tdgl_ctx *ctx, int kind) {
+    const int S = blk_depth(ctx), MI = ctx->max_iter;
+    const std::vector<int> &h = ctx->sweep_hist[kind];
+    int best = S;
+    double best_c = 1e300;
+    for (int a = S; a >= 1 && (int)h.size() == ctx->n * kHist; --a) {
+        double c = 0.0;
+        for (int i = 0; i < ctx->n; ++i)
+            for (int q = 0; q < kHist; ++q) {
+                const int sw = h[(size_t)i * kHist + q];
+                if (sw <= 0) continue;
+                const BlkPos b = blk_pos(a, S, MI, sw);
+                c += (double)ctx->inst[i].d.N * (b.pass + (sw == b.start + b.len ? 0 : 1));
+            }
+        if (c < best_c) {
+            best_c = c;
+            best = a;
+        }
+    }
+    return std::min(best, MI);
+}
+
 // The Jacobi iterations after the first sweep (already enqueued, its input
 // residual in row 0): sweep l reads row l-1 on the device and is a no-op
 // for instances whose solve has ended.  The work-group of each instance's
@@ -1204,7 +1306,7 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
     // hands over the rows below starts[k] not handed over before
     std::vector<int> starts{0};
     starts.reserve(MI + 1);
-    int remaining = n, launched = 1, polled = 0;
+    int remaining = n, launched = ctx->blk ? ctx->blk_a : 1, polled = 0;
     // two-sweep passes from l = 1 (schedule 1) or after one single sweep
     // from l = 2 (schedule 2), whichever the recent sweep counts favour
     const int kind = count_step ? 0 : 1;
@@ -1240,10 +1342,11 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
         if (remaining == 0 || launched >= MI) break;
         const int l = launched;
         const bool pair = ctx->fused && !(sched == 2 && l == 1);
-        const int nr = pair ? std::min(2, MI - l) : 1;
+        const int nr = std::min(ctx->blk ? blk_depth(ctx) : (pair ? 2 : 1), MI - l);
         {
             ProfScope ps(ctx, TDGL_K_SWEEP);
-            if (pair) launch_sweep2(ctx, l);
+            if (ctx->blk) launch_blk<MODE_SWEEP>(ctx, l, nr, l - starts.back(), (int)starts.size());
+            else if (pair) launch_sweep2(ctx, l);
             else launch_stencil<MODE_SWEEP>(ctx, l);
         }
         LAUNCHCHK();
@@ -1256,13 +1359,23 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
     {
         ProfScope ps(ctx, TDGL_K_OTHER);
         hipLaunchKernelGGL(k_solve_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, count_step,
-                           launched, sched, fin, ctx->pub_seq);
-        if (ctx->fused) launch_stencil<MODE_SWEEP>(ctx, -2);  // corrective sweep where needed
+                           launched, ctx->blk ? kBlkCode * blk_depth(ctx) + ctx->blk_a : sched, fin, ctx->pub_seq);
+        // corrective sweep where needed (of a block solve: where the host
+        // cannot rule it out)
+        if (ctx->fused) launch_stencil<MODE_SWEEP>(ctx, -2);
+        if (ctx->blk) {
+            bool fix = false;
+            for (int i = 0; i < n; ++i) {
+                const BlkPos b = blk_pos(ctx->blk_a, blk_depth(ctx), launched, conv_at[i] + 1);
+                fix = fix || deferred[i] || conv_at[i] + 1 != b.start + b.len;
+            }
+            if (fix) launch_blk<MODE_SWEEP>(ctx, -2, 0, 0, 0);
+        }
     }
     LAUNCHCHK();
     if (acc && sched == 2) acc->single_first_steps++;
     ctx->last_sweeps = deferred[0] ? -1 : conv_at[0] + 1;
-    if (ctx->fused) {
+    if (ctx->fused || ctx->blk) {
         // sweep counts the host has seen (capped or deferred solves left out)
         std::vector<int> &h = ctx->sweep_hist[kind];
         if ((int)h.size() != n * kHist) h.assign((size_t)n * kHist, -1);
@@ -1432,11 +1545,13 @@ void update_any_yz(tdgl_ctx *ctx) {
     }
     if (any != ctx->any_yz) drop_graph(ctx);
     ctx->any_yz = any;
+    if (zs != ctx->any_zseam) drop_graph(ctx);
     ctx->any_zseam = zs;
     if (any && ctx->persist) {
         drop_graph(ctx);
         ctx->persist = false;
     }
+    update_blk(ctx);
 }
 
 // One whole step of every instance as a fixed launch sequence with no host
@@ -1445,17 +1560,32 @@ void update_any_yz(tdgl_ctx *ctx) {
 // exits at once; the finalize kernel picks the first converged sweep), the
 // current and K update, the Poisson right side and a solve with every
 // multigrid cycle launched (each instance's cycles stop by themselves).
-tdgl_status enqueue_step_fixed(tdgl_ctx *ctx, int budget) {
+tdgl_status enqueue_step_fixed(tdgl_ctx *ctx, int budget, bool exact = false) {
     const int n = ctx->n;
     hipStream_t s = ctx->stream;
-    launch_assemble(ctx);
-    if (ctx->fused)
-        for (int l = 1; l < budget; l += 2) launch_sweep2(ctx, l);
-    else
-        for (int l = 1; l < budget; ++l) launch_stencil<MODE_SWEEP>(ctx, l);
-    hipLaunchKernelGGL(k_solve_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, 1, budget,
-                       ctx->fused ? 1 : 0, nullptr, 0u);
+    int code = ctx->fused ? 1 : 0;
+    if (ctx->blk) {
+        // exact: the solve is known to take `budget` sweeps
+        const int S = blk_depth(ctx);
+        ctx->blk_a = exact ? (budget - 1) % S + 1 : std::min(S, budget);
+        code = kBlkCode * S + ctx->blk_a;
+        launch_assemble(ctx);
+        int pass = 1, np = ctx->blk_a;
+        for (int l = ctx->blk_a; l < budget; l += S, ++pass) {
+            launch_blk<MODE_SWEEP>(ctx, l, std::min(S, budget - l), np, pass);
+            np = S;
+        }
+    } else {
+        launch_assemble(ctx);
+        if (ctx->fused)
+            for (int l = 1; l < budget; l += 2) launch_sweep2(ctx, l);
+        else
+            for (int l = 1; l < budget; ++l) launch_stencil<MODE_SWEEP>(ctx, l);
+    }
+    hipLaunchKernelGGL(k_solve_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, 1, budget, code, nullptr,
+                       0u);
     if (ctx->fused) launch_stencil<MODE_SWEEP>(ctx, -2);
+    if (ctx->blk && !exact) launch_blk<MODE_SWEEP>(ctx, -2, 0, 0, 0);
     LAUNCHCHK();
     if (!ctx->any_driven) return TDGL_OK;
     hipLaunchKernelGGL(k_jav_partial, dim3(ctx->tot_flat), dim3(256), 0, s, ctx->d_inst, ctx->d_pref_flat, n);
@@ -1935,6 +2065,7 @@ tdgl_status tdgl_step(tdgl_ctx *ctx, int nsteps, tdgl_step_stats *stats) {
     }
     for (int step = 0; step < nsteps; ++step) {
         // ---- Jacobi solve (all instances) --------------------------------
+        if (ctx->blk) ctx->blk_a = pick_blk_a(ctx, 0);
         {
             ProfScope ps(ctx, TDGL_K_ASSEMBLE);
             launch_assemble(ctx);
@@ -2160,6 +2291,7 @@ struct Tiling {
     int persist = 0;  // one cooperative launch per Jacobi solve
     int rhs4 = 0;     // Poisson right side on 64 x 16 tiles (four rows per thread)
     int tys = 0;      // rows of the two-sweep super-tiles (0: tys_default(rows))
+    int blk = 1;      // block solves in place of single sweeps, where the context has a block shape
 };
 
 tdgl_status apply_tiling(tdgl_ctx *ctx, const Tiling &t) {
@@ -2169,6 +2301,8 @@ tdgl_status apply_tiling(tdgl_ctx *ctx, const Tiling &t) {
     ctx->nt = t.nt != 0;
     ctx->fused = t.fused != 0 && !ctx->any_zseam;  // the two-sweep kernels have no z-seam phase
     ctx->persist = t.persist != 0 && !ctx->fused && !ctx->any_yz;
+    ctx->blk_on = t.blk != 0;
+    update_blk(ctx);
     for (auto &h : ctx->inst) set_tiling(h, t.rows, t.chunk, t.chunk2, t.tys);
     return upload_tiling(ctx);
 }
@@ -2197,11 +2331,11 @@ bool tune_file_lookup(const char *path, const std::string &key, Tiling *t, doubl
     bool found = false;
     while (fgets(line, sizeof line, f)) {
         char k[4000];
-        int r, c, nt, fu, pe, c2 = 0, r4 = 0, ty = 0;
+        int r, c, nt, fu, pe, c2 = 0, r4 = 0, ty = 0, bk = 1;
         double u;
-        // key rows chunk streaming fused persistent us [chunk2 [rhs4 [super-tile rows]]]
+        // key rows chunk streaming fused persistent us [chunk2 [rhs4 [super-tile rows [blocks]]]]
         const int got =
-            sscanf(line, "%3999s %d %d %d %d %d %lf %d %d %d", k, &r, &c, &nt, &fu, &pe, &u, &c2, &r4, &ty);
+            sscanf(line, "%3999s %d %d %d %d %d %lf %d %d %d %d", k, &r, &c, &nt, &fu, &pe, &u, &c2, &r4, &ty, &bk);
         if (got >= 7 && key == k && (r == 1 || r == 2 || r == 4) && c >= 0 && c2 >= 0 &&
             (nt == 0 || nt == 1) && (fu == 0 || fu == 1) && (pe == 0 || pe == 1) && (r4 == 0 || r4 == 1) &&
             (ty == 0 || ty == 16 || (ty == 32 && r >= 2))) {
@@ -2210,6 +2344,7 @@ bool tune_file_lookup(const char *path, const std::string &key, Tiling *t, doubl
             t->chunk2 = got >= 8 ? c2 : 0;
             t->rhs4 = got >= 9 ? r4 : 0;
             t->tys = got >= 10 ? ty : 0;
+            t->blk = got >= 11 ? (bk != 0) : 1;
             t->nt = nt;
             t->fused = fu;
             t->persist = pe;
@@ -2258,6 +2393,8 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
         // also the z run of the stencil passes (assemble, Poisson right
         // side, single sweeps) under the two-sweep candidates, which vary
         // only the super-tile kernel's own z run
+        Tiling best_single;
+        double best_single_us = 1e300;
         int stencil_chunk[2][5] = {};
         double stencil_us[2][5];
         for (auto &a : stencil_us) for (double &v : a) v = 1e300;
@@ -2304,7 +2441,32 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
                     best_us = us;
                     best = t;
                 }
+                if (!fu && us < best_single_us) {
+                    best_single_us = us;
+                    best_single = t;
+                }
             }
+        // block solves stand in for single sweeps on small grids
+        if (ctx->blk_shape >= 0 && !ctx->any_zseam) {
+            tdgl_status e = apply_tiling(ctx, best_single);
+            if (e) return e;
+            const int S = blk_depth(ctx), reps = 4;
+            launch_blk<MODE_SWEEP>(ctx, -1, S, 0, 0);  // warm-up
+            HIPCHK(hipEventRecord(e0, s));
+            for (int q = 0; q < reps; ++q) launch_blk<MODE_SWEEP>(ctx, -1, S, 0, 0);
+            HIPCHK(hipEventRecord(e1, s));
+            LAUNCHCHK();
+            HIPCHK(hipEventSynchronize(e1));
+            float ms = 0.f;
+            HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+            const double us = 1e3 * ms / reps / S;
+            if (us < best_us) {
+                best_us = us;
+                best = best_single;
+            } else if (!best.fused) {
+                best.blk = 0;
+            }
+        }
         // two-sweep passes: the stencil passes that remain (the assemble
         // every step, the Poisson right side, an occasional single sweep)
         // take the z run under which the assemble is fastest
@@ -2380,8 +2542,8 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
         if (cache_path) {
             FILE *f = fopen(cache_path, "a");
             if (f) {
-                fprintf(f, "%s %d %d %d %d %d %.3f %d %d %d\n", key.c_str(), best.rows, best.chunk, best.nt,
-                        best.fused, best.persist, best_us, best.chunk2, best.rhs4, best.tys);
+                fprintf(f, "%s %d %d %d %d %d %.3f %d %d %d %d\n", key.c_str(), best.rows, best.chunk, best.nt,
+                        best.fused, best.persist, best_us, best.chunk2, best.rhs4, best.tys, best.blk);
                 fclose(f);
             }
         }
@@ -2533,6 +2695,7 @@ tdgl_status adjoint_step(tdgl_ctx *c, const AdjLayout &L, int iprev, int inext, 
     hipLaunchKernelGGL(k_adj_reduce, dim3(1), dim3(256), 0, s, c->d_inst, G, 3, 0.0, L.adj);
     hipLaunchKernelGGL(k_adj_assemble, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psim, mum, newest, older, k >= 2 ? 1 : 0, L.adj);
     LAUNCHCHK();
+    c->blk_a = 1;  // k_adj_assemble's warm start stands for iterate 1
     e = jacobi_loop(c, nullptr, nullptr, 0);
     if (e) return e;
     // sources: eps gradient, mubar^-, K terms and psibar^-
@@ -2621,7 +2784,7 @@ tdgl_status voltage_grad_run(tdgl_ctx *ctx, int nsteps, int window_begin, int C,
                 // with no host round trip); spectral Poisson only, where the
                 // rest of the step is a fixed sequence too
                 const int sw = fw_sweeps[s0 + j - 1];
-                tdgl_status e = (sw > 0 && !ctx->any_mg && !ctx->persist) ? enqueue_step_fixed(ctx, sw)
+                tdgl_status e = (sw > 0 && !ctx->any_mg && !ctx->persist) ? enqueue_step_fixed(ctx, sw, true)
                                                                            : tdgl_step(ctx, 1, nullptr);
                 if (e) return e;
                 hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.seg_psi + (size_t)j * N,

@@ -76,7 +76,7 @@ __global__ void k_links(const Inst *__restrict__ insts, int which, const double 
 // which is the instance's max_iter or the nl sweeps launched, whichever is
 // smaller.  fused: 0 -- single sweeps; 1 -- the sweeps after the first ran
 // as two-sweep passes from l = 1; 2 -- one single sweep (l = 1), then
-// two-sweep passes from l = 2.
+// two-sweep passes from l = 2; kBlkCode S + a -- block launches (blk_pos).
 // Updates the psi buffer index and step counters and clears the residual
 // words for the next step.
 __global__ __launch_bounds__(FIN_THREADS) void k_solve_finalize(const Inst *__restrict__ insts, int ninst,
@@ -112,6 +112,13 @@ __global__ __launch_bounds__(FIN_THREADS) void k_solve_finalize(const Inst *__re
             if (!fused) {
                 st->cur ^= (sweeps & 1);
                 st->fix = 0;
+            } else if (fused >= kBlkCode) {
+                // only a launch's last iterate is stored: an earlier one is
+                // made again from the launch's input, into the buffer that
+                // launch wrote
+                const BlkPos b = blk_pos(fused % kBlkCode, fused / kBlkCode, nl, sweeps);
+                st->fix = (sweeps == b.start + b.len) ? 0 : sweeps - b.start;
+                st->cur ^= (b.pass + 1) & 1;
             } else {
                 // the iterates the passes store: psi^(1) and, from the
                 // pairs, those of the parity of the pairs' end (odd from
@@ -130,7 +137,7 @@ __global__ __launch_bounds__(FIN_THREADS) void k_solve_finalize(const Inst *__re
                 st->t += I.dt;
                 st->n += 1.0;
                 st->acc_sweeps += sweeps;
-                st->acc_passes += pass_count(fused, sweeps);
+                st->acc_passes += pass_count(fused >= kBlkCode ? 0 : fused, sweeps);
                 st->acc_capped += capped;
                 st->acc_sw_min = min(st->acc_sw_min, sweeps);
                 st->acc_sw_max = max(st->acc_sw_max, sweeps);

@@ -27,6 +27,19 @@ template <int MODE, int R, bool NT, bool YZ>
 __global__ void k_stencil(const Inst *insts, const int *prefix, int ninst, int l, const float2 *ext_in,
                           float2 *ext_out, unsigned long long *pub, unsigned seq);
 
+// Threads of k_blk: one per (x, y) column of the block with an S-node halo.
+__host__ __device__ constexpr int blk_threads(int bx, int by, int s) {
+    return ((bx + 2 * s) * (by + 2 * s) + 63) / 64 * 64;
+}
+template <int BX, int BY, int BZ, int S, int HZ, int MODE, bool YZ>
+__global__ void k_blk(const Inst *insts, const int *prefix, int ninst, int l, int ns, int np, int pass,
+                      unsigned long long *pub, unsigned seq);
+// block shapes: X(BX, BY, BZ, S, z halo)
+#define TDGL_BLK_VARIANTS(X) \
+    X(16, 8, 2, 2, 2)        \
+    X(32, 8, 4, 2, 2)        \
+    X(32, 16, 1, 4, 0)
+
 __global__ void k_links(const Inst *insts, int which, const double *Kp);
 __global__ void k_solve_finalize(const Inst *insts, int ninst, int count_step, int nl, int fused,
                                  unsigned long long *pub, unsigned seq);

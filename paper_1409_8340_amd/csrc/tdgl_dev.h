@@ -54,7 +54,7 @@ struct DevState {
     double frac;      // inclusion generator: covered fraction
     float mu_last_res;// Poisson residual max-norm at the end of the last solve
     int pad2;
-    int fix;          // two-sweep mode: the result needs the corrective sweep
+    int fix;          // iterates of the corrective pass the result needs (0: none)
     int pad3;
     // step statistics accumulated on the device (graph-replayed steps)
     double acc_sweeps, acc_capped, acc_mu_cycles, acc_mu_capped, acc_passes;
@@ -243,6 +243,21 @@ __host__ __device__ inline int pass_count(int fused, int s) {
     if (fused == 1) return s / 2;
     return s == 1 ? 0 : (s + 1) / 2;
 }
+
+// Launches of a block solve (k_blk): launch 0, the assemble, makes iterates
+// 1 .. a, launch 1 + j iterates a + j S + 1 .. (S of them, the last launch
+// what is left of nl); launch i reads psi[cur ^ (i & 1)] and writes the other
+// buffer.  The launch that makes iterate s, its first iterate's index minus
+// one and how many it makes.
+struct BlkPos {
+    int pass, start, len;
+};
+__host__ __device__ inline BlkPos blk_pos(int a, int S, int nl, int s) {
+    if (s <= a) return {0, 0, a};
+    const int j = (s - a - 1) / S, l = a + j * S;
+    return {1 + j, l, nl - l < S ? nl - l : S};
+}
+constexpr int kBlkCode = 16;  // k_solve_finalize's schedule code of a block solve: kBlkCode S + a
 
 // Slots (complex-value index of the b/M copy; (ht/2)/M follows it) of the
 // side copies of node (x, y, z), -1 where it is not beside a tile column:
