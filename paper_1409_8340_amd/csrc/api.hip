@@ -186,88 +186,7 @@ struct LevelHost {
 struct Hierarchy {
     std::vector<LevelHost> lev;
     bool ok = true;
-    // the coarsest level is solved directly (no axis beyond CO_DIRECT_MAX)
-    bool direct() const {
-        const LevelHost &L = lev.back();
-        return ok && std::max(L.n[0], std::max(L.n[1], L.n[2])) <= CO_DIRECT_MAX;
-    }
 };
-
-// Modes of one axis of a coarsest level (n <= CO_DIRECT_MAX): the 1D
-// finite-volume operator A u_i = ap_i (u_{i+1} - u_i) + am_i (u_{i-1} - u_i)
-// is symmetric in the control volumes V, so V^1/2 A V^-1/2 = Q lam Q^T by
-// cyclic Jacobi rotations (Golub and Van Loan, Sec. 8.5).  f[q n + i] =
-// (Q^T V^1/2)[i][q], b[q n + i] = (V^-1/2 Q)[i][q]; mode 0 is the constant
-// one (the largest eigenvalue, zero).
-struct AxisModes {
-    std::vector<double> f, b, lam;
-};
-
-AxisModes axis_modes(const AxisLevel &a) {
-    const int n = a.n;
-    std::vector<double> S((size_t)n * n, 0.0), Q((size_t)n * n, 0.0), sv(n);
-    auto wrap = [&](int i) { return i < 0 ? (a.per ? n - 1 : 0) : (i >= n ? (a.per ? 0 : n - 1) : i); };
-    for (int i = 0; i < n; ++i) sv[i] = std::sqrt(a.vol[i]);
-    for (int i = 0; i < n; ++i) {
-        const int ip = wrap(i + 1), im = wrap(i - 1);
-        S[(size_t)i * n + i] -= a.ap[i] + a.am[i];
-        S[(size_t)i * n + ip] += a.ap[i] * sv[i] / sv[ip];
-        S[(size_t)i * n + im] += a.am[i] * sv[i] / sv[im];
-        Q[(size_t)i * n + i] = 1.0;
-    }
-    for (int i = 0; i < n; ++i)
-        for (int j = 0; j < i; ++j) S[(size_t)i * n + j] = S[(size_t)j * n + i] =
-            0.5 * (S[(size_t)i * n + j] + S[(size_t)j * n + i]);
-    for (int sweep = 0; sweep < 60; ++sweep) {
-        double off = 0.0, all = 0.0;
-        for (int i = 0; i < n; ++i)
-            for (int j = 0; j < n; ++j) {
-                const double v = S[(size_t)i * n + j] * S[(size_t)i * n + j];
-                all += v;
-                if (i != j) off += v;
-            }
-        if (off <= 1e-34 * all) break;
-        for (int p = 0; p < n; ++p)
-            for (int q = p + 1; q < n; ++q) {
-                const double g = S[(size_t)p * n + q];
-                if (g == 0.0) continue;
-                const double th = (S[(size_t)q * n + q] - S[(size_t)p * n + p]) / (2.0 * g);
-                const double t = (th >= 0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(th * th + 1.0));
-                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-                for (int k = 0; k < n; ++k) {
-                    const double u = S[(size_t)k * n + p], v = S[(size_t)k * n + q];
-                    S[(size_t)k * n + p] = c * u - s * v;
-                    S[(size_t)k * n + q] = s * u + c * v;
-                }
-                for (int k = 0; k < n; ++k) {
-                    const double u = S[(size_t)p * n + k], v = S[(size_t)q * n + k];
-                    S[(size_t)p * n + k] = c * u - s * v;
-                    S[(size_t)q * n + k] = s * u + c * v;
-                }
-                for (int k = 0; k < n; ++k) {
-                    const double u = Q[(size_t)k * n + p], v = Q[(size_t)k * n + q];
-                    Q[(size_t)k * n + p] = c * u - s * v;
-                    Q[(size_t)k * n + q] = s * u + c * v;
-                }
-            }
-    }
-    std::vector<int> ord(n);
-    for (int i = 0; i < n; ++i) ord[i] = i;
-    std::sort(ord.begin(), ord.end(),
-              [&](int x, int y) { return S[(size_t)x * n + x] > S[(size_t)y * n + y]; });
-    AxisModes m;
-    m.f.resize((size_t)n * n);
-    m.b.resize((size_t)n * n);
-    m.lam.resize(n);
-    for (int i = 0; i < n; ++i) {
-        m.lam[i] = i == 0 ? 0.0 : S[(size_t)ord[i] * n + ord[i]];
-        for (int q = 0; q < n; ++q) {
-            m.f[(size_t)q * n + i] = Q[(size_t)q * n + ord[i]] * sv[q];
-            m.b[(size_t)i * n + q] = Q[(size_t)q * n + ord[i]] / sv[q];
-        }
-    }
-    return m;
-}
 
 Hierarchy build_hierarchy(const tdgl_params &p) {
     Hierarchy H;
@@ -506,8 +425,7 @@ struct tdgl_ctx {
     bool any_yz = false;              // some instance has a yz-plane field
     bool any_zseam = false;           // ... with By != 0 on a periodic z axis (single sweeps, no adjoint)
     bool any_fft = false, any_mg = false;
-    bool any_co_iter = false;  // some multigrid instance iterates on its coarsest level
-    size_t co_lds = 0;         // LDS of the direct coarsest solve (0: no instance takes it)
+    int co_nodes = 0;  // largest coarsest multigrid level
     bool any_driven = false;
     int max_iter = 1, max_cycles = 1;
     int rows = 2;     // stencil rows per thread
@@ -687,15 +605,6 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 L.tiles_z = cdiv(L.nz, L.chunk);
                 h.mg_blocks[l] = (int)(mtxy * L.tiles_z);
             }
-            if (!fft_eligible(p) && h.H.direct()) {
-                const LevelHost &LC = h.H.lev.back();
-                for (int a = 0; a < 3; ++a) {
-                    const size_t na = (size_t)LC.n[a];
-                    d.co_f[a] = cv.take<double>(na * na);
-                    d.co_b[a] = cv.take<double>(na * na);
-                    d.co_lam[a] = cv.take<double>(na);
-                }
-            }
             d.mu = d.lev[0].mu[0];
             d.f = d.lev[0].rhs;
             if (fft_eligible(p)) {
@@ -822,25 +731,8 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
             }
         }
     }
-    for (int i = 0; i < ctx->n; ++i) {
-        InstHost &h = ctx->inst[i];
-        if (!h.p.driven || h.d.fft) continue;
-        if (!h.d.co_f[0]) {
-            ctx->any_co_iter = true;
-            continue;
-        }
-        const LevelHost &LC = h.H.lev.back();
-        ctx->co_lds = std::max(ctx->co_lds, (size_t)2 * LC.N * sizeof(double));
-        for (int a = 0; a < 3; ++a) {
-            const AxisModes m = axis_modes(LC.ax[a]);
-            HIPCHK(hipMemcpy((void *)h.d.co_f[a], m.f.data(), m.f.size() * 8, hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy((void *)h.d.co_b[a], m.b.data(), m.b.size() * 8, hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy((void *)h.d.co_lam[a], m.lam.data(), m.lam.size() * 8, hipMemcpyHostToDevice));
-        }
-    }
-    if (ctx->co_lds)
-        HIPCHK(hipFuncSetAttribute((const void *)k_mg_coarsest_direct, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)ctx->co_lds));
+    for (const auto &h : ctx->inst)
+        if (h.p.driven && !h.d.fft) ctx->co_nodes = std::max(ctx->co_nodes, (int)h.H.lev.back().N);
     // prefix tables
     const int n = ctx->n;
     std::vector<int> ps(n + 1, 0), pf(n + 1, 0), pm((size_t)kMaxLevels * (n + 1), 0),
@@ -1155,11 +1047,12 @@ tdgl_status enqueue_vcycle(tdgl_ctx *c, int cyc) {
     }
     {
         ProfScope ps(c, TDGL_K_MG_COARSE);
-        if (c->co_lds)
-            hipLaunchKernelGGL(k_mg_coarsest_direct, dim3(n), dim3(CO_DIRECT_THREADS), c->co_lds, s, c->d_inst, n,
-                               cyc);
-        if (c->any_co_iter)
-            hipLaunchKernelGGL(k_mg_coarsest, dim3(n), dim3(CO_THREADS), 0, s, c->d_inst, n, cyc);
+        const dim3 th(std::min(CO_THREADS, (c->co_nodes + 63) / 64 * 64));
+        const size_t lds = (size_t)2 * c->co_nodes * sizeof(float);
+        if (c->co_nodes <= CO_THREADS)
+            hipLaunchKernelGGL(k_mg_coarsest<1>, dim3(n), th, lds, s, c->d_inst, n, cyc);
+        else
+            hipLaunchKernelGGL(k_mg_coarsest<4>, dim3(n), th, lds, s, c->d_inst, n, cyc);
     }
     for (int l = L - 2; l >= 0; --l) {
         ProfScope ps(c, l == 0 ? TDGL_K_MG_FINE : TDGL_K_MG_COARSE);

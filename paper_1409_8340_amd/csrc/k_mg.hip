@@ -250,156 +250,142 @@ __global__ __launch_bounds__(256) void k_mg_prolong(const Inst *__restrict__ ins
     }
 }
 
-// Coarsest level, solved directly where no axis is longer than
-// CO_DIRECT_MAX: the level operator is a sum of 1D finite-volume operators,
-// each symmetric in its control volumes V, so with its modes
-// A = V^-1/2 Q lam Q^T V^1/2 per axis the solution is three short
-// contractions to the modes, a division by the sum of the axes' eigenvalues
-// and three contractions back, in double precision in LDS.  The constant
-// mode is dropped, which projects the right side onto the range and gives
-// the result zero weighted mean.  One work-group per instance: a level of a
-// few hundred nodes is one load, six passes of (nx + ny + nz) / 3
-// multiply-adds a node and one store.  The Jacobi iteration below needs
-// hundreds of sweeps with a work-group reduction each: 465 us a solve on
-// average on the 12 x 8 x 3 nodes below 192 x 101 x 33, three quarters of
-// that box's step, against 7 us here.
-__global__ __launch_bounds__(CO_DIRECT_THREADS) void k_mg_coarsest_direct(const Inst *__restrict__ insts,
-                                                                          int ninst, int cyc) {
-    extern __shared__ double co_sm[];
-    const Inst &I = insts[blockIdx.x];
-    if (!I.driven || I.fft || !I.co_f[0] || mg_done(I, cyc)) return;
-    const int lv = I.nlev - 1;
-    const MGLevel &L = I.lev[lv];
-    const int N = L.N, nx = L.nx, ny = L.ny, nz = L.nz;
-    double *a = co_sm, *b = co_sm + N;
-    const double fm = (lv == 0) ? I.st->f_mean : 0.0;
-    for (int m = threadIdx.x; m < N; m += CO_DIRECT_THREADS) a[m] = (double)L.rhs[m] - fm;
-    __syncthreads();
-    // dst[.., i, ..] = sum_q T[q n + i] src[.., q, ..] along axis ax
-    auto contract = [&](int ax, const double *__restrict__ T, const double *src, double *dst) {
-        const int n = ax == 0 ? nx : (ax == 1 ? ny : nz);
-        const int st = ax == 0 ? 1 : (ax == 1 ? nx : nx * ny);
-        for (int m = threadIdx.x; m < N; m += CO_DIRECT_THREADS) {
-            const int i = (m / st) % n, m0 = m - i * st;
-            double s = 0.0;
-            for (int q = 0; q < n; ++q) s += T[q * n + i] * src[m0 + q * st];
-            dst[m] = s;
-        }
-        __syncthreads();
-    };
-    contract(0, I.co_f[0], a, b);
-    contract(1, I.co_f[1], b, a);
-    contract(2, I.co_f[2], a, b);
-    for (int m = threadIdx.x; m < N; m += CO_DIRECT_THREADS) {
-        const int x = m % nx, y = (m / nx) % ny, z = m / (nx * ny);
-        b[m] = m == 0 ? 0.0 : b[m] / (I.co_lam[0][x] + I.co_lam[1][y] + I.co_lam[2][z]);
-    }
-    __syncthreads();
-    contract(2, I.co_b[2], b, a);
-    contract(1, I.co_b[1], a, b);
-    contract(0, I.co_b[0], b, a);
-    for (int m = threadIdx.x; m < N; m += CO_DIRECT_THREADS) L.mu[0][m] = (float)a[m];
-}
-
-// Coarsest level with a longer axis: one work-group per instance iterates Jacobi sweeps in
-// double precision (in the level's two buffers) until the residual falls
-// below 1e-6 of the right side or 4000 sweeps, after projecting the right
-// side onto the range (zero volume-weighted mean) and shifting the result to
-// zero mean.  Result in mu[0].  The level may be the finest one (tiny grids):
-// then its right side is f minus its weighted mean and the iterate starts
-// from the stored mu.
+// Coarsest level: one work-group per instance iterates Jacobi sweeps in
+// double precision on an FP32 iterate until the residual falls below 1e-6 of
+// the right side or 4000 sweeps, after projecting the right side onto the
+// range (zero volume-weighted mean) and shifting the result to zero mean.
+// Result in mu[0].  The level may be the finest one (tiny grids): then its
+// right side is f minus its weighted mean and the iterate starts from the
+// stored mu.
+// The iterate sits in LDS (two buffers of N floats), a thread keeps its
+// nodes' coefficients and right sides in registers, and a sweep ends at one
+// barrier with a vote on the residual, since only whether the maximum exceeds
+// the threshold matters.  Through global memory, with the maximum reduced
+// every sweep over 1024 threads, a solve took 465 us on average on the 12 x 8
+// x 3 nodes below 192 x 101 x 33, three quarters of that box's step.  The
+// values are those of that form, bit for bit: the quotient by D is its
+// reciprocal's product corrected once with the exact remainder, which rounds
+// as the division does (Markstein, IBM J. Res. Dev. 34, 1990).  (A direct
+// solve through the axes' modes takes 7 us, but what it takes away from the
+// stop rule's error reaches the ninth digit of K.)
+// NPT: nodes per thread (1 where N fits the work-group, else 4).
+template <int NPT>
 __global__ __launch_bounds__(CO_THREADS) void k_mg_coarsest(const Inst *__restrict__ insts,
                                                             int ninst, int cyc) {
+    extern __shared__ float co_sm[];
     __shared__ double red[CO_THREADS / 64];
-    __shared__ double sh_mean, sh_rmax;
+    __shared__ double sh_v;
+    __shared__ int open[3];
     const Inst &I = insts[blockIdx.x];
-    if (!I.driven || I.fft || I.co_f[0] || mg_done(I, cyc)) return;
+    if (!I.driven || I.fft || mg_done(I, cyc)) return;
     const int lv = I.nlev - 1;
     const MGLevel &L = I.lev[lv];
-    const int N = L.N;
+    const int N = L.N, nt = (int)blockDim.x, nw = nt >> 6;
     const double fm = (lv == 0) ? I.st->f_mean : 0.0;
-    // volume-weighted mean of the right side
+    float *a = co_sm, *bq = co_sm + N;
+    auto sum = [&](double v) {
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+        __syncthreads();
+        double s = 0.0;
+        for (int i = 0; i < nw; ++i) s += red[i];
+        return s;
+    };
+    int at[NPT][7];                      // the node and its six neighbours
+    double co[NPT][6], D[NPT], rD[NPT], V[NPT], d0[NPT];
     double s = 0.0;
-    for (int m = threadIdx.x; m < N; m += CO_THREADS) {
-        const int x = m % L.nx, y = (m / L.nx) % L.ny, z = m / (L.nx * L.ny);
-        const double V = (double)L.vol[0][x] * L.vol[1][y] * L.vol[2][z];
-        s += V * ((double)L.rhs[m] - fm);
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        const int m = (int)threadIdx.x + i * nt, mm = m < N ? m : 0;
+        const int x = mm % L.nx, y = (mm / L.nx) % L.ny, z = mm / (L.nx * L.ny);
+        const int xm = wrapi(x - 1, L.nx, L.per[0]), xp = wrapi(x + 1, L.nx, L.per[0]);
+        const int ym = wrapi(y - 1, L.ny, L.per[1]), yp = wrapi(y + 1, L.ny, L.per[1]);
+        const int zm = wrapi(z - 1, L.nz, L.per[2]), zp = wrapi(z + 1, L.nz, L.per[2]);
+        const int nx = L.nx, nxy = L.nx * L.ny;
+        at[i][0] = z * nxy + y * nx + xp;
+        at[i][1] = z * nxy + y * nx + xm;
+        at[i][2] = z * nxy + yp * nx + x;
+        at[i][3] = z * nxy + ym * nx + x;
+        at[i][4] = zp * nxy + y * nx + x;
+        at[i][5] = zm * nxy + y * nx + x;
+        at[i][6] = mm;
+        co[i][0] = (double)L.ap[0][x];
+        co[i][1] = (double)L.am[0][x];
+        co[i][2] = (double)L.ap[1][y];
+        co[i][3] = (double)L.am[1][y];
+        co[i][4] = (double)L.ap[2][z];
+        co[i][5] = (double)L.am[2][z];
+        D[i] = -((double)L.ap[0][x] + L.am[0][x] + L.ap[1][y] + L.am[1][y] + L.ap[2][z] + L.am[2][z]);
+        rD[i] = D[i] != 0.0 ? 1.0 / D[i] : 0.0;  // 0: the node keeps its value
+        V[i] = (double)L.vol[0][x] * L.vol[1][y] * L.vol[2][z];
+        d0[i] = (double)L.rhs[mm] - fm;
+        // volume-weighted mean of the right side
+        if (m < N) s += V[i] * d0[i];
+        if (m < N) a[m] = lv != 0 ? 0.f : L.mu[0][m];
     }
-    s = wg_sum<CO_THREADS>(s, red);
-    if (threadIdx.x == 0) sh_mean = s / L.vsum;
-    __syncthreads();
-    const double rmean = sh_mean;
+    if (threadIdx.x < 3) open[threadIdx.x] = 0;
+    s = sum(s);
+    const double rmean = s / L.vsum;
     double rnorm = 0.0;
-    for (int m = threadIdx.x; m < N; m += CO_THREADS)
-        rnorm = fmax(rnorm, fabs((double)L.rhs[m] - fm - rmean));
-    // max over the group
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        d0[i] -= rmean;
+        if ((int)threadIdx.x + i * nt < N) rnorm = fmax(rnorm, fabs(d0[i]));
+    }
     for (int o = 32; o > 0; o >>= 1) rnorm = fmax(rnorm, __shfl_xor(rnorm, o, 64));
+    __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = rnorm;
     __syncthreads();
     if (threadIdx.x == 0) {
         double mx = 0.0;
-        for (int i = 0; i < CO_THREADS / 64; ++i) mx = fmax(mx, red[i]);
-        sh_rmax = mx;
+        for (int i = 0; i < nw; ++i) mx = fmax(mx, red[i]);
+        sh_v = mx;
     }
     __syncthreads();
-    const double thr = 1e-6 * sh_rmax;
-    float *a = L.mu[0], *bq = L.mu[1];
-    if (lv != 0)
-        for (int m = threadIdx.x; m < N; m += CO_THREADS) a[m] = 0.f;
-    __syncthreads();
+    const double thr = 1e-6 * sh_v;
+    int ph = 0;  // sweep index mod 3
     for (int it = 0; it < 4000; ++it) {
-        double rloc = 0.0;
-        for (int m = threadIdx.x; m < N; m += CO_THREADS) {
-            const int x = m % L.nx, y = (m / L.nx) % L.ny, z = m / (L.nx * L.ny);
-            const int xm = wrapi(x - 1, L.nx, L.per[0]), xp = wrapi(x + 1, L.nx, L.per[0]);
-            const int ym = wrapi(y - 1, L.ny, L.per[1]), yp = wrapi(y + 1, L.ny, L.per[1]);
-            const int zm = wrapi(z - 1, L.nz, L.per[2]), zp = wrapi(z + 1, L.nz, L.per[2]);
-            const double mc = a[m];
-            const long nx = L.nx, nxy = (long)L.nx * L.ny;
-            const double Amu = (double)L.ap[0][x] * (a[z * nxy + y * nx + xp] - mc) +
-                               (double)L.am[0][x] * (a[z * nxy + y * nx + xm] - mc) +
-                               (double)L.ap[1][y] * (a[z * nxy + yp * nx + x] - mc) +
-                               (double)L.am[1][y] * (a[z * nxy + ym * nx + x] - mc) +
-                               (double)L.ap[2][z] * (a[zp * nxy + y * nx + x] - mc) +
-                               (double)L.am[2][z] * (a[zm * nxy + y * nx + x] - mc);
-            const double D = -((double)L.ap[0][x] + L.am[0][x] + L.ap[1][y] + L.am[1][y] +
-                               L.ap[2][z] + L.am[2][z]);
-            const double r = ((double)L.rhs[m] - fm - rmean) - Amu;
-            rloc = fmax(rloc, fabs(r));
-            bq[m] = (D != 0.0) ? (float)(mc + 0.9 * r / D) : (float)mc;
+        bool over = false;
+#pragma unroll
+        for (int i = 0; i < NPT; ++i) {
+            const double mc = a[at[i][6]];
+            const double Amu = co[i][0] * (a[at[i][0]] - mc) + co[i][1] * (a[at[i][1]] - mc) +
+                               co[i][2] * (a[at[i][2]] - mc) + co[i][3] * (a[at[i][3]] - mc) +
+                               co[i][4] * (a[at[i][4]] - mc) + co[i][5] * (a[at[i][5]] - mc);
+            const double r = d0[i] - Amu;
+            const double x = 0.9 * r, q = x * rD[i];
+            const double quo = __builtin_fma(__builtin_fma(-q, D[i], x), rD[i], q);
+            if ((int)threadIdx.x + i * nt < N) {
+                over = over || fabs(r) > thr;
+                bq[at[i][6]] = (rD[i] != 0.0) ? (float)(mc + quo) : (float)mc;
+            }
         }
-        for (int o = 32; o > 0; o >>= 1) rloc = fmax(rloc, __shfl_xor(rloc, o, 64));
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = rloc;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double mx = 0.0;
-            for (int i = 0; i < CO_THREADS / 64; ++i) mx = fmax(mx, red[i]);
-            sh_rmax = mx;
-        }
+        if (__ballot(over) != 0 && (threadIdx.x & 63) == 0) open[ph] = 1;
         __syncthreads();
         // swap roles
         float *t = a;
         a = bq;
         bq = t;
-        if (sh_rmax <= thr) break;
-        __syncthreads();
+        if (!open[ph]) break;
+        // the word of the sweep after next: its last readers passed this barrier
+        const int p2 = ph == 0 ? 2 : ph - 1;
+        if (threadIdx.x == 0) open[p2] = 0;
+        ph = ph == 2 ? 0 : ph + 1;
     }
     // shift to zero weighted mean and leave the result in mu[0]
     double sm = 0.0;
-    for (int m = threadIdx.x; m < N; m += CO_THREADS) {
-        const int x = m % L.nx, y = (m / L.nx) % L.ny, z = m / (L.nx * L.ny);
-        sm += (double)L.vol[0][x] * L.vol[1][y] * L.vol[2][z] * a[m];
-    }
-    sm = wg_sum<CO_THREADS>(sm, red);
-    if (threadIdx.x == 0) sh_mean = sm / L.vsum;
-    __syncthreads();
-    const float mmean = (float)sh_mean;
-    for (int m = threadIdx.x; m < N; m += CO_THREADS) {
-        const float v = a[m] - mmean;
-        L.mu[0][m] = v;
-    }
+#pragma unroll
+    for (int i = 0; i < NPT; ++i)
+        if ((int)threadIdx.x + i * nt < N) sm += V[i] * a[at[i][6]];
+    sm = sum(sm);
+    const float mmean = (float)(sm / L.vsum);
+#pragma unroll
+    for (int i = 0; i < NPT; ++i)
+        if ((int)threadIdx.x + i * nt < N) L.mu[0][at[i][6]] = a[at[i][6]] - mmean;
 }
+template __global__ void k_mg_coarsest<1>(const Inst *, int, int);
+template __global__ void k_mg_coarsest<4>(const Inst *, int, int);
 
 // End of a Poisson solve: number of cycles and final residual; clears the
 // cycle words.  One thread per instance.

@@ -64,10 +64,8 @@ __global__ void k_mg_restrict(const Inst *insts, const int *prefix, int ninst, i
                               float omega);
 __global__ void k_mg_prolong(const Inst *insts, const int *prefix, int ninst, int lv, int ifine,
                              int cyc);
+template <int NPT>
 __global__ void k_mg_coarsest(const Inst *insts, int ninst, int cyc);
-__global__ void k_mg_coarsest_direct(const Inst *insts, int ninst, int cyc);
-constexpr int CO_DIRECT_MAX = 64;      // longest axis of a coarsest level that is solved directly
-constexpr int CO_DIRECT_THREADS = 512;
 __global__ void k_mg_finalize(const Inst *insts, int ninst, int count_step);
 __global__ void k_mu_mean_partial(const Inst *insts, const int *prefix, int ninst, int which);
 

@@ -157,11 +157,6 @@ struct Inst {
                          // (periodic y, ny a multiple of the super-tile height); else they start one tile row in
     int nlev;
     MGLevel lev[kMaxLevels];
-    // direct solve of the coarsest multigrid level (null: iterated instead):
-    // per axis the 1D operator's modes, co_f[q n + i] = (Q^T V^1/2)[i][q]
-    // (nodes q to mode i) and co_b[q n + i] = (V^-1/2 Q)[i][q] (modes q to
-    // node i), and its eigenvalues, mode 0 the constant one
-    const double *co_f[3], *co_b[3], *co_lam[3];
     // direct spectral Poisson solve (periodic x and y, open z)
     int fft;             // 1: the Poisson equation is solved by FFT, 0: by multigrid
     int nxrad, nyrad;    // FFT radix plans along x and y

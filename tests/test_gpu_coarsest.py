@@ -1,5 +1,5 @@
-"""The multigrid's coarsest level solved directly, where that level is the
-whole grid: tdgl_poisson_solve against the oracle's exact solution."""
+"""The multigrid's coarsest level, where that level is the whole grid:
+tdgl_poisson_solve against the oracle's exact solution."""
 import numpy as np
 import pytest
 
@@ -11,9 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,open_,g,hy", [
-    ((64, 4, 2), (False, True, True), 1.0, 0.5),     # the longest axis solved directly
+    ((64, 4, 2), (False, True, True), 1.0, 0.5),
     ((63, 4, 2), (False, True, True), 1.0, 0.5),     # odd periodic axis
-    ((65, 3, 2), (False, True, True), 1.0, 0.5),     # one beyond: iterated instead
+    ((65, 3, 2), (False, True, True), 1.0, 0.5),
+    ((15, 13, 11), (False, False, False), 1.0, 0.5),  # more nodes than threads: no axis coarsens
     ((8, 8, 8), (False, False, False), 2.0, 0.4),    # all periodic, anisotropic
     ((2, 64, 4), (False, True, True), 1.0, 0.3),     # two nodes on a periodic axis
     ((7, 1, 1), (False, True, True), 1.0, 0.5),      # one-node open axes
@@ -22,9 +23,8 @@ pytestmark = pytest.mark.gpu
     ((192, 13, 9), (False, True, True), 1.0, 0.5),   # below four finer levels
 ])
 def test_coarsest_level_vs_exact(shape, open_, g, hy):
-    # a single level leaves the FP32 storage of f and mu (6e-8 each, amplified
-    # by the spread of the modes, below 100 here); with finer levels the
-    # residual stop 1e-7 adds as much
+    # FP32 storage of f and mu (6e-8 each, amplified by the spread of the
+    # modes, below 100 here) and the residual stop 1e-7
     import torch
     nx, ny, nz = shape
     grid = O.Grid(nx, ny, nz, 0.5, hy, 0.5, open_, g)
