@@ -420,6 +420,7 @@ struct tdgl_ctx {
     size_t fx_lds = 0, fy_lds = 0, fz_lds = 0;
     int fz_nzmax = 0;  // deepest z over the instances: scan rows per lane of the z solve
     bool fx_p2 = true, fy_p2 = true;  // every spectral instance has power-of-two nx (ny)
+    bool fft_yz = false;              // y transforms and z systems in one kernel (kx-major half spectrum)
     bool fx_long = false;             // some spectral instance has nx > FFT_X_PTS
     bool noisy = false;               // some instance has a Langevin term
     bool any_yz = false;              // some instance has a yz-plane field
@@ -489,6 +490,11 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
     const int npad = (n + 63) / 64 * 64;
     unsigned *res = cv.take<unsigned>((size_t)max_iter * NSLOT * npad);
     unsigned *mures = cv.take<unsigned>((size_t)max_cycles * NSLOT * npad);
+    // the fused y and z pass of the spectral solve, when every spectral
+    // instance fits it
+    bool yz = true;
+    for (int i = 0; i < n; ++i)
+        if (fft_eligible(params[i])) yz = yz && fft_yz_planes(params[i].nx, params[i].ny, params[i].nz) > 0;
     for (int i = 0; i < n; ++i) {
         const tdgl_params &p = params[i];
         InstHost &h = ih[i];
@@ -618,16 +624,17 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 d.twy = cv.take<float2>(p.ny);
                 d.zip = cv.take<double>((size_t)p.ny * P * p.nz);
                 {
-                    // groups of fft_x_pairs row pairs; up to eight per
-                    // work-group while at least 2048 groups' work remain
-                    const long groups = cdiv((long)p.ny * p.nz, 2L * fft_x_pairs(p.nx));
+                    // fft_x_pairs row pairs of a plane per group; up to eight
+                    // groups per work-group while at least 2048 remain
+                    const long groups = (long)cdiv(p.ny, 2L * fft_x_pairs(p.nx, p.ny)) * p.nz;
                     d.fxg = (int)std::max(1L, std::min(8L, groups / 2048));
-                    h.fx_blocks = (int)cdiv(groups, (long)d.fxg);
+                    h.fx_blocks = cdiv(groups, d.fxg);
                 }
-                h.fy_blocks = fft_y_plan(p.nx, p.ny, p.nz).blocks;
+                d.fyz = yz ? fft_yz_planes(p.nx, p.ny, p.nz) : 0;
+                h.fy_blocks = d.fyz ? cdiv(P, d.fyz) : fft_y_plan(p.nx, p.ny, p.nz).blocks;
                 h.fz_blocks = p.nz <= FFT_ZSERIAL ? cdiv(p.ny * P, 256) : p.ny * cdiv(P, FFT_ZTK);
             }
-            part_cap = std::max(part_cap, h.mg_blocks[0]);
+            part_cap = std::max(part_cap, std::max(h.mg_blocks[0], h.fx_blocks));
         }
         d.part = cv.take<double>(part_cap);
         d.part_cap = part_cap;
@@ -707,6 +714,31 @@ int blk_depth(const tdgl_ctx *c) { return kBlkShapes[c->blk_shape].S; }
 // tiling on a grid small enough, and no z-seam phase (which k_blk has not).
 void update_blk(tdgl_ctx *c) { c->blk = c->blk_on && c->blk_shape >= 0 && !c->fused && !c->persist && !c->any_zseam; }
 
+// Forward (rows from src; SRC_PSI with the fused y and z pass only) and
+// inverse x transform of the context's spectral solve.
+const void *fft_fwd_fn(const tdgl_ctx *c, int src) {
+    if (c->fx_long)
+        return c->fx_p2 ? (const void *)k_fft_fwd<true, 4 * FFT_X_PTS, SRC_F, false>
+                        : (const void *)k_fft_fwd<false, 4 * FFT_X_PTS, SRC_F, false>;
+    if (!c->fft_yz)
+        return c->fx_p2 ? (const void *)k_fft_fwd<true, FFT_X_PTS, SRC_F, false>
+                        : (const void *)k_fft_fwd<false, FFT_X_PTS, SRC_F, false>;
+#define TDGL_FFT_FN(P2)                                                            \
+    (src == SRC_F ? (const void *)k_fft_fwd<P2, FFT_X_PTS, SRC_F, true>              \
+                  : (src == SRC_PSI ? (const void *)k_fft_fwd<P2, FFT_X_PTS, SRC_PSI, true> \
+                                    : (const void *)k_fft_fwd<P2, FFT_X_PTS, SRC_PSI_YZ, true>))
+    return c->fx_p2 ? TDGL_FFT_FN(true) : TDGL_FFT_FN(false);
+#undef TDGL_FFT_FN
+}
+const void *fft_inv_fn(const tdgl_ctx *c) {
+    if (c->fx_long)
+        return c->fx_p2 ? (const void *)k_fft_inv<true, 4 * FFT_X_PTS, false>
+                        : (const void *)k_fft_inv<false, 4 * FFT_X_PTS, false>;
+    if (c->fft_yz)
+        return c->fx_p2 ? (const void *)k_fft_inv<true, FFT_X_PTS, true> : (const void *)k_fft_inv<false, FFT_X_PTS, true>;
+    return c->fx_p2 ? (const void *)k_fft_inv<true, FFT_X_PTS, false> : (const void *)k_fft_inv<false, FFT_X_PTS, false>;
+}
+
 tdgl_status upload_tables(tdgl_ctx *ctx) {
     for (int i = 0; i < ctx->n; ++i) {
         InstHost &h = ctx->inst[i];
@@ -744,12 +776,11 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         pf[i + 1] = pf[i] + h.flat_blocks;
         nps[i] = h.st_blocks;
         npf[i] = h.flat_blocks;
-        npm[i] = h.p.driven ? h.mg_blocks[0] : 0;
+        npm[i] = !h.p.driven ? 0 : (h.d.fft ? h.fx_blocks : h.mg_blocks[0]);
         const bool mg = h.p.driven && !h.d.fft;
         for (int l = 0; l < kMaxLevels; ++l) {
             const size_t o = (size_t)l * (n + 1) + i;
-            // level 0 "all" also drives the mean of mu for every driven instance
-            const int b = (h.p.driven && l < h.d.nlev && (mg || l == 0)) ? h.mg_blocks[l] : 0;
+            const int b = (mg && l < h.d.nlev) ? h.mg_blocks[l] : 0;
             const int bm = (mg && l + 1 < h.d.nlev) ? h.mg_blocks[l] : 0;
             pm[o + 1] = pm[o] + b;
             pmid[o + 1] = pmid[o] + bm;
@@ -761,9 +792,11 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         ctx->fz_nzmax = std::max(ctx->fz_nzmax, h.p.nz);
         if (h.d.fft) {
             ctx->any_fft = true;
-            ctx->fx_lds = std::max(ctx->fx_lds, (size_t)(fft_x_pairs(h.p.nx) + 1) * h.p.nx * 8);
-            ctx->fy_lds = std::max(ctx->fy_lds, ((size_t)fft_y_plan(h.p.nx, h.p.ny, h.p.nz).TK *
-                                                      fft_y_stride(h.p.ny) + h.p.ny) * 8);
+            ctx->fft_yz = h.d.fyz > 0;
+            ctx->fx_lds = std::max(ctx->fx_lds, (size_t)fft_x_lds(h.p.nx, h.p.ny) * 8);
+            ctx->fy_lds = std::max(ctx->fy_lds, h.d.fyz ? (size_t)fft_yz_lds(h.p.ny, h.p.nz, h.d.fyz) * 8
+                                                        : ((size_t)fft_y_plan(h.p.nx, h.p.ny, h.p.nz).TK *
+                                                               fft_y_stride(h.p.ny) + h.p.ny) * 8);
             ctx->fx_p2 = ctx->fx_p2 && (h.p.nx & (h.p.nx - 1)) == 0;
             ctx->fx_long = ctx->fx_long || h.p.nx > FFT_X_PTS;
             ctx->fy_p2 = ctx->fy_p2 && (h.p.ny & (h.p.ny - 1)) == 0;
@@ -800,13 +833,15 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
     ctx->tot_fy = pfy[n];
     ctx->tot_fz = pfz[n];
     if (ctx->any_fft) {
-        for (const void *fn : {(const void *)k_fft_x<false, FFT_X_PTS>, (const void *)k_fft_x<true, FFT_X_PTS>,
-                                (const void *)k_fft_x<false, 4 * FFT_X_PTS>, (const void *)k_fft_x<true, 4 * FFT_X_PTS>})
-            HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ctx->fx_lds));
-        HIPCHK(hipFuncSetAttribute((const void *)k_fft_y<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)ctx->fy_lds));
-        HIPCHK(hipFuncSetAttribute((const void *)k_fft_y<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)ctx->fy_lds));
+        auto lds = [](const void *fn, size_t bytes) {
+            return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        };
+        for (int src = SRC_F; src <= SRC_PSI_YZ; ++src) HIPCHK(lds(fft_fwd_fn(ctx, src), ctx->fx_lds));
+        HIPCHK(lds(fft_inv_fn(ctx), ctx->fx_lds));
+        if (ctx->fft_yz)
+            HIPCHK(lds(ctx->fy_p2 ? (const void *)k_fft_yz<true> : (const void *)k_fft_yz<false>, ctx->fy_lds));
+        else
+            HIPCHK(lds(ctx->fy_p2 ? (const void *)k_fft_y<true> : (const void *)k_fft_y<false>, ctx->fy_lds));
         for (const void *fn : {(const void *)k_fft_zsolve<2>, (const void *)k_fft_zsolve<4>})
             HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ctx->fz_lds));
     }
@@ -1312,51 +1347,92 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
 // instances take the five FFT / z-solve passes; multigrid instances take
 // V-cycles until their stop rule, decided on the device and polled by the
 // host one cycle behind.  Statistics are accumulated into acc.
-// The five passes of the spectral solve for every instance that uses it.
-tdgl_status enqueue_fft(tdgl_ctx *ctx) {
+// The passes of the spectral solve for every instance that uses it: three
+// with the fused y and z pass, five otherwise.  step: the right side of a time
+// step, from psi; else the stored I.f.  Leaves the partials of the mean of mu.
+tdgl_status enqueue_fft(tdgl_ctx *ctx, bool step) {
     if (!ctx->any_fft) return TDGL_OK;
     const int n = ctx->n;
     hipStream_t s = ctx->stream;
     ProfScope ps(ctx, TDGL_K_MG_FINE);
-    const float *nf = nullptr;
-    float *nm = nullptr;
-    const dim3 gx(std::max(ctx->tot_fx, 1)), gy(std::max(ctx->tot_fy, 1)), bt(FFT_XY_THREADS), bx(FFT_X_THREADS);
-    auto xpass = [&](int dir) {
-        const void *fn = ctx->fx_long ? (ctx->fx_p2 ? (const void *)k_fft_x<true, 4 * FFT_X_PTS>
-                                                    : (const void *)k_fft_x<false, 4 * FFT_X_PTS>)
-                                      : (ctx->fx_p2 ? (const void *)k_fft_x<true, FFT_X_PTS>
-                                                    : (const void *)k_fft_x<false, FFT_X_PTS>);
-        const Inst *ins = ctx->d_inst;
-        const int *pref = ctx->d_pref_fx;
-        int nn = n, d = dir;
-        void *args[] = {(void *)&ins, (void *)&pref, (void *)&nn, (void *)&d, (void *)&nf, (void *)&nm};
-        (void)hipLaunchKernel(fn, gx, bx, args, ctx->fx_lds, s);
-    };
-    auto ypass = [&](int dir) {
-        if (ctx->fy_p2) hipLaunchKernelGGL(k_fft_y<true>, gy, bt, ctx->fy_lds, s, ctx->d_inst, ctx->d_pref_fy, n, dir);
-        else hipLaunchKernelGGL(k_fft_y<false>, gy, bt, ctx->fy_lds, s, ctx->d_inst, ctx->d_pref_fy, n, dir);
-    };
-    xpass(-1);
-    ypass(-1);
-    // up to 64 planes two rows per lane, else four (32-lane segments up to
-    // 128 planes, 64-lane ones beyond)
-    if (ctx->fz_nzmax <= 64)
-        hipLaunchKernelGGL(k_fft_zsolve<2>, dim3(std::max(ctx->tot_fz, 1)), dim3(256), ctx->fz_lds, s, ctx->d_inst,
-                           ctx->d_pref_fz, n);
-    else
-        hipLaunchKernelGGL(k_fft_zsolve<4>, dim3(std::max(ctx->tot_fz, 1)), dim3(256), ctx->fz_lds, s, ctx->d_inst,
-                           ctx->d_pref_fz, n);
-    ypass(+1);
-    xpass(+1);
+    const dim3 gx(std::max(ctx->tot_fx, 1)), gy(std::max(ctx->tot_fy, 1)), bx(FFT_X_THREADS);
+    const Inst *ins = ctx->d_inst;
+    const int *pref = ctx->d_pref_fx;
+    int nn = n;
+    const float *in = nullptr;
+    const int src = !step || !ctx->fft_yz ? SRC_F : (ctx->any_yz ? SRC_PSI_YZ : SRC_PSI);
+    {
+        void *args[] = {(void *)&ins, (void *)&pref, (void *)&nn, (void *)&in};
+        (void)hipLaunchKernel(fft_fwd_fn(ctx, src), gx, bx, args, ctx->fx_lds, s);
+    }
+    if (ctx->fft_yz) {
+        const dim3 bt(FFT_YZ_THREADS);
+        if (ctx->fy_p2) hipLaunchKernelGGL(k_fft_yz<true>, gy, bt, ctx->fy_lds, s, ctx->d_inst, ctx->d_pref_fy, n);
+        else hipLaunchKernelGGL(k_fft_yz<false>, gy, bt, ctx->fy_lds, s, ctx->d_inst, ctx->d_pref_fy, n);
+    } else {
+        const dim3 bt(FFT_XY_THREADS);
+        auto ypass = [&](int dir) {
+            if (ctx->fy_p2)
+                hipLaunchKernelGGL(k_fft_y<true>, gy, bt, ctx->fy_lds, s, ctx->d_inst, ctx->d_pref_fy, n, dir);
+            else
+                hipLaunchKernelGGL(k_fft_y<false>, gy, bt, ctx->fy_lds, s, ctx->d_inst, ctx->d_pref_fy, n, dir);
+        };
+        ypass(-1);
+        // up to 64 planes two rows per lane, else four (32-lane segments up to
+        // 128 planes, 64-lane ones beyond)
+        if (ctx->fz_nzmax <= 64)
+            hipLaunchKernelGGL(k_fft_zsolve<2>, dim3(std::max(ctx->tot_fz, 1)), dim3(256), ctx->fz_lds, s,
+                               ctx->d_inst, ctx->d_pref_fz, n);
+        else
+            hipLaunchKernelGGL(k_fft_zsolve<4>, dim3(std::max(ctx->tot_fz, 1)), dim3(256), ctx->fz_lds, s,
+                               ctx->d_inst, ctx->d_pref_fz, n);
+        ypass(+1);
+    }
+    {
+        void *args[] = {(void *)&ins, (void *)&pref, (void *)&nn};
+        (void)hipLaunchKernel(fft_inv_fn(ctx), gx, bx, args, ctx->fx_lds, s);
+    }
     LAUNCHCHK();
     return TDGL_OK;
 }
 
-tdgl_status enqueue_poisson(tdgl_ctx *ctx, tdgl_step_stats *acc) {
+// The weighted mean of mu of every driven instance: partials of the multigrid
+// instances (the spectral ones have left theirs), then the sums.
+void enqueue_mu_mean(tdgl_ctx *ctx) {
+    const int n = ctx->n;
+    if (ctx->any_mg)
+        hipLaunchKernelGGL(k_mu_mean_partial, dim3(std::max(ctx->tot_mg[0], 1)), dim3(256), 0, ctx->stream,
+                           ctx->d_inst, pref_mg(ctx, 0), n, 0);
+    hipLaunchKernelGGL(k_reduce_to_state, dim3(n), dim3(256), 0, ctx->stream, ctx->d_inst, ctx->d_np_mg0, 1, 1);
+}
+
+// The weighted mean of a given right side f, which the multigrid projects out
+// (the spectral solve drops the constant mode itself).
+void enqueue_f_mean(tdgl_ctx *ctx) {
+    if (!ctx->any_mg) return;
+    hipLaunchKernelGGL(k_mu_mean_partial, dim3(std::max(ctx->tot_mg[0], 1)), dim3(256), 0, ctx->stream, ctx->d_inst,
+                       pref_mg(ctx, 0), ctx->n, 1);
+    hipLaunchKernelGGL(k_reduce_to_state, dim3(ctx->n), dim3(256), 0, ctx->stream, ctx->d_inst, ctx->d_np_mg0, 4, 2);
+}
+
+// The right side of a time step where a pass of its own makes it: for
+// multigrid instances, with its weighted mean, and for spectral ones whose
+// spectrum is too large for the fused y and z pass.  There the forward x
+// transform could make it from psi as well, but its work-groups then hold 136
+// registers and 875 us pass at 1024 x 1024 x 128 against 413 + 272 us for the
+// two passes; on 300 x 180 x 50 it takes 26 us against 15 + 15.
+void enqueue_rhs(tdgl_ctx *ctx) {
+    if (!ctx->any_mg && ctx->fft_yz) return;
+    launch_rhs(ctx);
+    if (ctx->any_mg)
+        hipLaunchKernelGGL(k_reduce_to_state, dim3(ctx->n), dim3(256), 0, ctx->stream, ctx->d_inst, rhs_parts(ctx), 0, 2);
+}
+
+tdgl_status enqueue_poisson(tdgl_ctx *ctx, tdgl_step_stats *acc, bool step) {
     const int n = ctx->n;
     hipStream_t s = ctx->stream;
     const size_t RW = ctx->row_words();
-    tdgl_status fe = enqueue_fft(ctx);
+    tdgl_status fe = enqueue_fft(ctx, step);
     if (fe) return fe;
     std::vector<int> mconv_at(n, 0);
     if (ctx->any_mg) {
@@ -1395,9 +1471,7 @@ tdgl_status enqueue_poisson(tdgl_ctx *ctx, tdgl_step_stats *acc) {
         ProfScope ps(ctx, TDGL_K_OTHER);
         if (ctx->any_mg)
             hipLaunchKernelGGL(k_mg_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, acc ? 1 : 0);
-        hipLaunchKernelGGL(k_mu_mean_partial, dim3(std::max(ctx->tot_mg[0], 1)), dim3(256), 0, s, ctx->d_inst,
-                           pref_mg(ctx, 0), n, 0);
-        hipLaunchKernelGGL(k_reduce_to_state, dim3(n), dim3(256), 0, s, ctx->d_inst, ctx->d_np_mg0, 1, 1);
+        enqueue_mu_mean(ctx);
     }
     LAUNCHCHK();
     if (acc && ctx->any_mg) {
@@ -1483,10 +1557,9 @@ tdgl_status enqueue_step_fixed(tdgl_ctx *ctx, int budget, bool exact = false) {
     if (!ctx->any_driven) return TDGL_OK;
     hipLaunchKernelGGL(k_jav_partial, dim3(ctx->tot_flat), dim3(256), 0, s, ctx->d_inst, ctx->d_pref_flat, n);
     hipLaunchKernelGGL(k_kupdate, dim3(n), dim3(256), 0, s, ctx->d_inst, ctx->d_np_flat);
-    launch_rhs(ctx);
-    hipLaunchKernelGGL(k_reduce_to_state, dim3(n), dim3(256), 0, s, ctx->d_inst, rhs_parts(ctx), 0, 1);
+    enqueue_rhs(ctx);
     LAUNCHCHK();
-    tdgl_status e = enqueue_fft(ctx);
+    tdgl_status e = enqueue_fft(ctx, true);
     if (e) return e;
     if (ctx->any_mg) {
         for (int cyc = 0; cyc < ctx->max_cycles; ++cyc) {
@@ -1495,9 +1568,7 @@ tdgl_status enqueue_step_fixed(tdgl_ctx *ctx, int budget, bool exact = false) {
         }
         hipLaunchKernelGGL(k_mg_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, 1);
     }
-    hipLaunchKernelGGL(k_mu_mean_partial, dim3(std::max(ctx->tot_mg[0], 1)), dim3(256), 0, s, ctx->d_inst,
-                       pref_mg(ctx, 0), n, 0);
-    hipLaunchKernelGGL(k_reduce_to_state, dim3(n), dim3(256), 0, s, ctx->d_inst, ctx->d_np_mg0, 1, 1);
+    enqueue_mu_mean(ctx);
     LAUNCHCHK();
     return TDGL_OK;
 }
@@ -1976,11 +2047,10 @@ tdgl_status tdgl_step(tdgl_ctx *ctx, int nsteps, tdgl_step_stats *stats) {
             }
             {
                 ProfScope ps(ctx, TDGL_K_RHS);
-                launch_rhs(ctx);
-                hipLaunchKernelGGL(k_reduce_to_state, dim3(n), dim3(256), 0, s, ctx->d_inst, rhs_parts(ctx), 0, 1);
+                enqueue_rhs(ctx);
             }
             LAUNCHCHK();
-            tdgl_status e = enqueue_poisson(ctx, &acc);
+            tdgl_status e = enqueue_poisson(ctx, &acc, true);
             if (e) return e;
         }
         acc.steps++;
@@ -2086,12 +2156,9 @@ tdgl_status tdgl_poisson_solve(tdgl_ctx *ctx, const float *f, float *mu) {
     if (!d.driven) return fail(TDGL_ESTATE, "the instance is not driven: it has no Poisson solver");
     hipStream_t s = ctx->stream;
     HIPCHK(hipMemcpyAsync(d.f, f, (size_t)d.N * 4, hipMemcpyDeviceToDevice, s));
-    // weighted mean of f for the multigrid right side
-    hipLaunchKernelGGL(k_mu_mean_partial, dim3(std::max(ctx->tot_mg[0], 1)), dim3(256), 0, s, ctx->d_inst,
-                       pref_mg(ctx, 0), 1, 1);
-    hipLaunchKernelGGL(k_reduce_to_state, dim3(1), dim3(256), 0, s, ctx->d_inst, ctx->d_np_mg0, 4, 1);
+    enqueue_f_mean(ctx);
     LAUNCHCHK();
-    tdgl_status e = enqueue_poisson(ctx, nullptr);
+    tdgl_status e = enqueue_poisson(ctx, nullptr, false);
     if (e) return e;
     hipLaunchKernelGGL(k_mu_io, dim3(fill_grid(d.N)), dim3(256), 0, s, ctx->d_inst, 0, mu, 1);
     LAUNCHCHK();
@@ -2409,11 +2476,10 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
                 best_us = pus;
             }
         }
-        // the Poisson right side on the chosen tile or on 64 x 16 tiles with
-        // four rows per thread, whichever runs faster
-        bool any_driven = false;
-        for (const auto &h : ctx->inst) any_driven = any_driven || h.p.driven;
-        if (any_driven && best.rows != 4) {
+        // the Poisson right side, where a pass of its own makes it, on the
+        // chosen tile or on 64 x 16 tiles with four rows per thread,
+        // whichever runs faster
+        if ((ctx->any_mg || (ctx->any_fft && !ctx->fft_yz)) && best.rows != 4) {
             float rms[2];
             for (int q4 = 0; q4 < 2; ++q4) {
                 Tiling t = best;
@@ -2565,11 +2631,9 @@ tdgl_status adjoint_step(tdgl_ctx *c, const AdjLayout &L, int iprev, int inext, 
     const double *Km = L.seg_K + iprev, *Kn = L.seg_K + inext;
     // Poisson transpose: fbar = W G(W^-1 mubar)
     hipLaunchKernelGGL(k_adj_prep_f, dim3(G), dim3(256), 0, s, c->d_inst, L.mubar);
-    hipLaunchKernelGGL(k_mu_mean_partial, dim3(std::max(c->tot_mg[0], 1)), dim3(256), 0, s, c->d_inst,
-                       pref_mg(c, 0), 1, 1);
-    hipLaunchKernelGGL(k_reduce_to_state, dim3(1), dim3(256), 0, s, c->d_inst, c->d_np_mg0, 4, 1);
+    enqueue_f_mean(c);
     LAUNCHCHK();
-    tdgl_status e = enqueue_poisson(c, nullptr);
+    tdgl_status e = enqueue_poisson(c, nullptr, false);
     if (e) return e;
     // adjoint of the Poisson right side, links at K_n
     hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, c->d_inst, 1, Kn);

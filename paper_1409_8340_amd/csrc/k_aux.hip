@@ -311,10 +311,12 @@ __global__ __launch_bounds__(256) void k_kupdate(const Inst *__restrict__ insts,
 // 3 = psi2 (mean |psi|^2), 4 = f_mean (from volume-weighted sums).
 __global__ __launch_bounds__(256) void k_reduce_to_state(const Inst *__restrict__ insts,
                                                          const int *__restrict__ nparts, int field,
-                                                         int driven_only) {
+                                                         int which) {
     __shared__ double red[4];
     const Inst &I = insts[blockIdx.x];
-    if (driven_only && !I.driven) return;
+    // which: 0 every instance, 1 driven ones, 2 multigrid ones
+    if (which && !I.driven) return;
+    if (which == 2 && I.fft) return;
     const double s = wg_reduce_parts(I.part, nparts[blockIdx.x], red);
     if (threadIdx.x == 0) {
         DevState *st = I.st;

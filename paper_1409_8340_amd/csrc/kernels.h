@@ -46,7 +46,7 @@ __global__ void k_solve_finalize(const Inst *insts, int ninst, int count_step, i
 __global__ void k_acc_reset(const Inst *insts, int ninst);
 __global__ void k_jav_partial(const Inst *insts, const int *prefix, int ninst);
 __global__ void k_kupdate(const Inst *insts, const int *nparts);
-__global__ void k_reduce_to_state(const Inst *insts, const int *nparts, int field, int driven_only);
+__global__ void k_reduce_to_state(const Inst *insts, const int *nparts, int field, int which);
 __global__ void k_psi2_partial(const Inst *insts, const int *prefix, int ninst);
 __global__ void k_fill_c(float2 *p, long n, float re, float im);
 __global__ void k_fill_f(float *p, long n, float v);
@@ -69,15 +69,23 @@ __global__ void k_mg_coarsest(const Inst *insts, int ninst, int cyc);
 __global__ void k_mg_finalize(const Inst *insts, int ninst, int count_step);
 __global__ void k_mu_mean_partial(const Inst *insts, const int *prefix, int ninst, int which);
 
-template <bool P2, int XC>
-__global__ void k_fft_x(const Inst *insts, const int *prefix, int ninst, int dir, const float *in_ext,
-                        float *out_ext);
+// rows of the forward x transform: a real array, or the right side made from psi
+enum { SRC_F = 0, SRC_PSI = 1, SRC_PSI_YZ = 2 };
+template <bool P2, int XC, int SRC, bool TR>
+__global__ void k_fft_fwd(const Inst *insts, const int *prefix, int ninst, const float *in_ext);
+template <bool P2, int XC, bool TR>
+__global__ void k_fft_inv(const Inst *insts, const int *prefix, int ninst);
+template <bool P2>
+__global__ void k_fft_yz(const Inst *insts, const int *prefix, int ninst);
 template <bool P2>
 __global__ void k_fft_y(const Inst *insts, const int *prefix, int ninst, int dir);
 template <int RMAX>
 __global__ void k_fft_zsolve(const Inst *insts, const int *prefix, int ninst);
 __global__ void k_fft_tables(const Inst *insts, int inst);
-__host__ __device__ int fft_x_pairs(int nx);
+__host__ __device__ int fft_x_pairs(int nx, int ny);
+__host__ __device__ int fft_x_lds(int nx, int ny);
+__host__ __device__ int fft_yz_planes(int nx, int ny, int nz);
+__host__ __device__ int fft_yz_lds(int ny, int nz, int g);
 __host__ __device__ int fft_y_stride(int ny);
 struct FftYPlan {
     int G;       // whole planes per tile (ntk = 1)
@@ -94,6 +102,11 @@ constexpr int FFT_ZSERIAL = 16; // up to this nz one lane solves a whole z syste
 constexpr int FFT_MAXN = 8192;  // points per work-group of the x and y passes
 constexpr int FFT_XY_THREADS = 1024;  // threads per work-group of the y passes
 constexpr int FFT_X_THREADS = 256;    // threads per work-group of the x passes
+constexpr int FFT_YZ_THREADS = 1024;  // threads per work-group of the fused y and z pass
+constexpr int FFT_YZ_TARGET = 1024;   // its points per work-group, where several kx planes fit
+constexpr int FFT_YZ_PTS = 16384;     // and at most
+constexpr int FFT_YZ_BATCH = 8192;    // points it transforms at a time
+constexpr int FFT_YZ_LDS = 18432;     // its LDS, complex elements (144 KB)
 constexpr int FFT_X_PTS = 1024;       // complex points per work-group of the x passes (target)
 
 __global__ void k_adj_save(const Inst *insts, float2 *dpsi, float *dmu, double *dK, int raw);

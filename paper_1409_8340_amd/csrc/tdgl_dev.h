@@ -163,7 +163,8 @@ struct Inst {
     int xrad[16], yrad[16];
     float2 *spec;        // half spectrum, nz * ny rows of pitch sp >= nx/2 + 1
     int sp;              // row pitch of spec (complex elements)
-    int fxg;             // row-pair groups per work-group of the x passes (their loads overlap the transforms)
+    int fxg;             // groups per work-group of the x passes (the next group's loads overlap the transform)
+    int fyz;             // kx planes per work-group of the fused y and z pass (0: separate passes)
     int fcpt;            // cells per thread of the flat reductions (J_av, |psi|^2)
     float2 *twx, *twy;   // twiddles exp(-2 pi i k / n) along x and y
     double *zip;         // Thomas pivots of the z systems, ny * (nx/2 + 1) columns of nz
