@@ -24,6 +24,8 @@
 
 #include <hip/hip_cooperative_groups.h>
 
+#include <type_traits>
+
 namespace tdgl {
 
 // MODE selects the pass; R is the number of consecutive rows a thread owns
@@ -85,7 +87,8 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     const int x0 = txi * TX, y0 = tyi * TYv;
     const int k0 = tzi * chunk;
     const int k1 = min(k0 + chunk, I.nz);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: so are the links of its rows
     const int x = x0 + lane;
     const int nx = I.nx, ny = I.ny, nz = I.nz;
     const unsigned NXY = (unsigned)nx * (unsigned)ny;
@@ -107,16 +110,18 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     const float cx = I.cx, cy = I.cy, cz = I.cz;
     float2 ux[ROWS], uz[ROWS];
     bool vy[ROWS];
-    CellSrc own[ROWS];
+    int off[ROWS], mode[ROWS];  // cell_src() of the thread's nodes; px and fac follow from x and ux
     bool all_plain = true;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         const int y = y0 + w * ROWS + r;
         vy[r] = (x < nx) && (y < ny);
-        ux[r] = (y < ny) ? I.ux[y] : make_float2(1.f, 0.f);
-        uz[r] = (y < ny) ? I.uz[y] : make_float2(1.f, 0.f);
-        own[r] = cell_src(I, x, y);
-        all_plain = all_plain && own[r].mode == SRC_PLAIN;
+        ux[r] = to_scalar((y < ny) ? I.ux[y] : make_float2(1.f, 0.f));
+        uz[r] = to_scalar((y < ny) ? I.uz[y] : make_float2(1.f, 0.f));
+        const CellSrc o = cell_src(I, x, y);
+        off[r] = o.off;
+        mode[r] = o.mode;
+        all_plain = all_plain && o.mode == SRC_PLAIN;
     }
     const bool hthr = threadIdx.x < HALOv;
     int hgx = 0, hgy = 0, hlx = 0, hly = 0;
@@ -125,57 +130,89 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
         halo_cell<TYv>(threadIdx.x, x0, y0, hgx, hgy, hlx, hly);
         hs = cell_src(I, hgx, hgy);
     }
-    auto own_plane = [&](int p, float2 *out) {
-        // own cells of plane p (p = -1: no such plane -> zeros)
-        if (p < 0) {
+    all_plain = __ballot(!all_plain) == 0 && __ballot(hthr && hs.mode != SRC_PLAIN) == 0;
+    const bool zper = I.per[2] != 0;
+    // plane behind v, -1: none (v one plane outside the grid at most)
+    auto zpl = [&](int v) -> int { return (unsigned)v < (unsigned)nz ? v : (zper ? (v < 0 ? nz - 1 : 0) : -1); };
+    // Every load is issued a plane ahead of its use and unconditionally (one
+    // that is not needed, past the run or beyond an open face, reads the
+    // tile's first node from every lane), into the registers that its
+    // predecessor has just left: no second set of them, no branch around a
+    // load.  A plane's base address is scalar, the offsets in it stay the same.
+    // The waves of a mid-size grid wait for memory most of their lives, so
+    // what counts is how many are resident: with the row links scalar too, a
+    // sweep of two rows per thread needs 79 registers where it took 86 (6
+    // waves per SIMD, 5 before), one of four 120 where it took 140 (4, 3).
+    // Two and three planes ahead cost more waves than they hide.  Per step,
+    // one / two / three planes ahead, and before: 24 instances to 128 x 96 x
+    // 48 nodes, sweeps 801 / 847 / 853, 1015 us; 384 x 240 x 48 with a yz
+    // field 348 / 375 / 392, 372 us; assemble at 1024 x 1024 x 128 1108 us,
+    // 1241 before.
+    const unsigned hoff = (unsigned)hs.off;
+    auto load_psi = [&](int v, bool need, float2 *f) {
+        const int p = need ? zpl(v) : -1;
+        const gf2 *base = src + (size_t)(p < 0 ? k0 : p) * NXY;
+        const unsigned msk = p < 0 ? 0u : ~0u;
 #pragma unroll
-            for (int r = 0; r < ROWS; ++r) out[r] = make_float2(0.f, 0.f);
-            return;
-        }
-        const unsigned pb = (unsigned)p * NXY;
-        if (all_plain) {
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) out[r] = ld2(src, pb + (unsigned)own[r].off);
-        } else {
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) out[r] = fetch<YZ>(src, Pt, pb, p, nx, own[r], I.wz);
-        }
+        for (int r = 0; r < ROWS; ++r) f[r] = ld2(base, (unsigned)off[r] & msk);
     };
-
-    // prologue: registers for planes k0-1, k0, k0+1; LDS buffer 0 = plane k0
-    float2 pm[ROWS], pc[ROWS], pn[ROWS];
-    own_plane(zplane(I, k0, -1), pm);
-    own_plane(k0, pc);
-    own_plane(zplane(I, k0, +1), pn);
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) lds[0][1 + w * ROWS + r][1 + lane] = pc[r];
-    if (hthr) lds[0][hly][hlx] = fetch<YZ>(src, Pt, (unsigned)k0 * NXY, k0, nx, hs, I.wz);
-    float2 hv = make_float2(0.f, 0.f);
-    if (hthr && k0 + 1 < k1) hv = fetch<YZ>(src, Pt, (unsigned)(k0 + 1) * NXY, k0 + 1, nx, hs, I.wz);
-
-    // per-plane streams of the first plane
-    float2 bh[ROWS], dh[ROWS];
-    float ep[ROWS], mu[ROWS];
-    const float mu_mean = (is_first_mode(MODE) && I.driven) ? (float)st->mu_mean : 0.f;
-    auto load_streams = [&](int k, float2 *bh_, float2 *dh_, float *ep_, float *mu_) {
-        const unsigned pb = (unsigned)k * NXY;
+    auto load_halo = [&](int v, bool need, float2 &h) {
+        const gf2 *base = src + (size_t)(need ? v : k0) * NXY;
+        h = ld2(base, need ? hoff : 0u);
+    };
+    auto load_streams = [&](int k, bool need, float2 *bh_, float2 *dh_, float *ep_, float *mu_) {
+        const size_t pb = (size_t)(need ? k : k0) * NXY;
+        const unsigned msk = need ? ~0u : 0u;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const unsigned m = pb + (unsigned)own[r].off;
+            const unsigned m = (unsigned)off[r] & msk;
             if (MODE == MODE_SWEEP) {
-                bh_[r] = vy[r] ? (NT ? ld2nt(bhp, m) : ld2(bhp, m)) : make_float2(0.f, 0.f);
-                dh_[r] = vy[r] ? (NT ? ld2nt(dhp, m) : ld2(dhp, m)) : make_float2(0.f, 0.f);
+                bh_[r] = NT ? ld2nt(bhp + pb, m) : ld2(bhp + pb, m);
+                dh_[r] = NT ? ld2nt(dhp + pb, m) : ld2(dhp + pb, m);
             }
             if (is_first_mode(MODE) || MODE == MODE_ENERGY)
-                ep_[r] = vy[r] ? (NT ? __builtin_nontemporal_load(&epsp[m]) : float(epsp[m])) : 0.f;
+                ep_[r] = NT ? __builtin_nontemporal_load(&(epsp + pb)[m]) : float((epsp + pb)[m]);
             if (is_first_mode(MODE))
-                mu_[r] = (vy[r] && I.driven) ? (NT ? __builtin_nontemporal_load(&mup[m]) : float(mup[m])) - mu_mean : 0.f;
+                mu_[r] = I.driven ? (NT ? __builtin_nontemporal_load(&(mup + pb)[m]) : float((mup + pb)[m])) : 0.f;
         }
     };
-    load_streams(k0, bh, dh, ep, mu);
+    // own values of plane v from loaded ones (boundary rules where there are any)
+    auto settle_own = [&](int v, const float2 *f, float2 *out) {
+        if (all_plain) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) out[r] = f[r];
+        } else {
+            const int p = max(zpl(v), 0);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                // beyond an open x face at x = nx: conj(ux^2), see cell_src
+                const float2 u2 = xcmul(ux[r], ux[r]);
+                const CellSrc o{off[r], mode[r], mode[r] == SRC_FAC ? 1 : x, make_float2(u2.x, -u2.y)};
+                out[r] = settle<YZ>(Pt, p, nx, o, f[r], I.wz);
+            }
+        }
+    };
 
+    float2 f[ROWS], h;                        // psi of plane k + 1 as loaded and its halo
+    float2 bh[ROWS], dh[ROWS];                // the streams of plane k
+    float ep[ROWS], mu[ROWS];
+    float2 pm[ROWS], pc[ROWS];
+    {
+        float2 fm[ROWS], fc[ROWS], hc;
+        load_psi(k0, true, fc);
+        load_halo(k0, true, hc);
+        load_psi(k0 - 1, true, fm);
+        load_psi(k0 + 1, true, f);
+        load_halo(k0 + 1, k0 + 1 < k1, h);
+        load_streams(k0, true, bh, dh, ep, mu);
+        settle_own(k0, fc, pc);
+        settle_own(k0 - 1, fm, pm);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) lds[0][1 + w * ROWS + r][1 + lane] = pc[r];
+        if (hthr) lds[0][hly][hlx] = settle<YZ>(Pt, k0, nx, hs, hc, I.wz);
+    }
+    const float mu_mean = (is_first_mode(MODE) && I.driven) ? (float)st->mu_mean : 0.f;
     const float ht2 = I.ht2, S2 = I.S2, u = I.u;
-    const bool zper = I.per[2] != 0;
     // a yz field on a periodic z axis: the z neighbours across the wrap
     // carry the seam phase, psi_{-1} = zs psi_{nz-1} and psi_{nz} =
     // conj(zs) psi_0 (zs = 1 for any other field)
@@ -183,7 +220,7 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     // Langevin draws of this step (assemble only): step counter before the step
     const bool noise = (MODE == MODE_FIRSTN) && I.zeta_max > 0.f;
     const unsigned long long nstep = noise ? (unsigned long long)st->n : 0ull;
-    float rmax = 0.f;
+    unsigned rmaxb = 0;
     double acc = 0.0;
     // assemble under a two-sweep tiling: slots in the side copies of b/M and
     // (ht/2)/M of this thread's first row at z = 0 (-1: its column x is not
@@ -194,22 +231,16 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
 
     for (int k = k0; k < k1; ++k) {
         const int buf = (k - k0) & 1;
-        const unsigned pbase = (unsigned)k * NXY;
-        // issue the next planes' loads before the barrier
-        float2 pnn[ROWS], bhn[ROWS], dhn[ROWS];
-        float epn[ROWS], mun[ROWS];
-        float2 hvn = make_float2(0.f, 0.f);
-        if (k + 1 < k1) {
-            own_plane(zplane(I, k + 1, +1), pnn);
-            load_streams(k + 1, bhn, dhn, epn, mun);
-            if (hthr && k + 2 < k1) hvn = fetch<YZ>(src, Pt, (unsigned)(k + 2) * NXY, k + 2, nx, hs, I.wz);
-        }
+        float2 pn[ROWS];
+        settle_own(k + 1, f, pn);
         __syncthreads();  // plane k staged; the other buffer is free
         if (k + 1 < k1) {
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) lds[buf ^ 1][1 + w * ROWS + r][1 + lane] = pn[r];
-            if (hthr) lds[buf ^ 1][hly][hlx] = hv;
+            if (hthr) lds[buf ^ 1][hly][hlx] = all_plain ? h : settle<YZ>(Pt, k + 1, nx, hs, h, I.wz);
         }
+        load_psi(k + 2, k + 2 <= k1, f);
+        load_halo(k + 2, k + 2 < k1, h);
         const bool zm = (k > 0) || zper, zp = (k < nz - 1) || zper;
         float2 pmk[ROWS], pnk[ROWS];
 #pragma unroll
@@ -237,83 +268,94 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) uxk[r] = ux[r];
         }
+        const size_t pbase = (size_t)k * NXY;
+        auto rows = [&](auto in) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const int ly = 1 + w * ROWS + r;
-            const float2 c = pc[r];
-            const float2 xm = lds[buf][ly][lane], xp = lds[buf][ly][lane + 2];
-            const float2 ym = lds[buf][ly - 1][lane + 1], yp = lds[buf][ly + 1][lane + 1];
-            if (!vy[r]) continue;
-            const unsigned m = pbase + (unsigned)own[r].off;
-            if (MODE == MODE_ENERGY) {
-                // forward edges only; an edge beyond an open face does not exist.
-                const float a2 = cabs2(c);
-                const int y = y0 + w * ROWS + r;
-                const bool fx = I.per[0] || x < nx - 1, fy = I.per[1] || y < ny - 1;
-                const float wxn = (!I.per[0] && nx > 1 && (x == 0 || x == nx - 1)) ? 0.5f : 1.f;
-                const float wyn = (!I.per[1] && ny > 1 && (y == 0 || y == ny - 1)) ? 0.5f : 1.f;
-                const float wzn = (!zper && nz > 1 && (k == 0 || k == nz - 1)) ? 0.5f : 1.f;
-                double e = (double)(wxn * wyn * wzn) * (double)(-ep[r] * a2 + 0.5f * a2 * a2);
-                if (fx) e += (double)(wyn * wzn * cx) * (double)cabs2(csub(cmul(uxk[r], xp), c));
-                if (fy) e += (double)(wxn * wzn * cy) * (double)cabs2(csub(yp, c));
-                if (zp) e += (double)(wxn * wyn * cz) * (double)cabs2(csub(cmul(uz[r], pnk[r]), c));
-                acc += e;
-                continue;
-            }
-            // off-diagonal neighbour sum NS of the covariant Laplacian
-            // (Eq. LaplUV_xz), open faces doubling the inner neighbour.
-            const float2 ns = nsum(uxk[r], uz[r], xm, xp, ym, yp, pmk[r], pnk[r], zm, zp, cx, cy, cz);
-            if (MODE == MODE_NS) {
-                st2(nsout, m, ns);
-                continue;
-            }
-            if (MODE == MODE_RHS) {
-                // f = sum_a (1/h_a^2) Im[psi^* (U psi_+ + U^* psi_-)] = Im[psi^* NS]
-                const float f = rhs_node(c, ns);
-                fw[m] = f;
-                acc += (double)f * (double)node_w(I, x, y0 + w * ROWS + r, k);
-                continue;
-            }
-            float2 nw;
-            if (is_first_mode(MODE)) {
-                float2 bhv, dhv;
-                float r2;
-                const float2 zz = noise ? langevin2(I, m, nstep) : make_float2(0.f, 0.f);
-                assemble_node(c, ep[r], u * mu[r], ns, S2, ht2, noise, zz, bhv, dhv, nw, r2);
-                if (NT) {
-                    st2nt(bhw, m, bhv);
-                    st2nt(dhw, m, dhv);
-                } else {
-                    st2(bhw, m, bhv);
-                    st2(dhw, m, dhv);
+            for (int r = 0; r < ROWS; ++r) {
+                const int ly = 1 + w * ROWS + r;
+                const float2 c = pc[r];
+                const float2 xm = lds[buf][ly][lane], xp = lds[buf][ly][lane + 2];
+                const float2 ym = lds[buf][ly - 1][lane + 1], yp = lds[buf][ly + 1][lane + 1];
+                const unsigned m = (unsigned)off[r];
+                if (MODE == MODE_ENERGY) {
+                    if (!vy[r]) continue;
+                    // forward edges only; an edge beyond an open face does not exist.
+                    const float a2 = cabs2(c);
+                    const int y = y0 + w * ROWS + r;
+                    const bool fx = I.per[0] || x < nx - 1, fy = I.per[1] || y < ny - 1;
+                    const float wxn = (!I.per[0] && nx > 1 && (x == 0 || x == nx - 1)) ? 0.5f : 1.f;
+                    const float wyn = (!I.per[1] && ny > 1 && (y == 0 || y == ny - 1)) ? 0.5f : 1.f;
+                    const float wzn = (!zper && nz > 1 && (k == 0 || k == nz - 1)) ? 0.5f : 1.f;
+                    double e = (double)(wxn * wyn * wzn) * (double)(-ep[r] * a2 + 0.5f * a2 * a2);
+                    if (fx) e += (double)(wyn * wzn * cx) * (double)cabs2(csub(cmul(uxk[r], xp), c));
+                    if (fy) e += (double)(wxn * wzn * cy) * (double)cabs2(csub(yp, c));
+                    if (zp) e += (double)(wxn * wyn * cz) * (double)cabs2(csub(cmul(uz[r], pnk[r]), c));
+                    acc += e;
+                    continue;
                 }
-                // side copies for the two-sweep super-tiles (one 16-byte
-                // global store each)
-                if (eL >= 0) st4(I.edge, (unsigned)eL + 2u * r + eplane * k, bhv, dhv);
-                if (eR >= 0) st4(I.edge, (unsigned)eR + 2u * r + eplane * k, bhv, dhv);
-                rmax = (r2 > rmax || r2 != r2) ? r2 : rmax;
-            } else {
-                nw = jacobi(bh[r], dh[r], ns);
-                const float r2 = resid2(nw, c, dh[r], ht2);
-                rmax = (r2 > rmax || r2 != r2) ? r2 : rmax;
+                // off-diagonal neighbour sum NS of the covariant Laplacian
+                // (Eq. LaplUV_xz), open faces doubling the inner neighbour.
+                float2 ns;
+                if constexpr (decltype(in)::value)
+                    ns = nsum_in(uxk[r], uz[r], xm, xp, ym, yp, pmk[r], pnk[r], cx, cy, cz);
+                else
+                    ns = nsum(uxk[r], uz[r], xm, xp, ym, yp, pmk[r], pnk[r], zm, zp, cx, cy, cz);
+                if (MODE == MODE_NS) {
+                    if (vy[r]) st2(nsout + pbase, m, ns);
+                    continue;
+                }
+                if (MODE == MODE_RHS) {
+                    // f = sum_a (1/h_a^2) Im[psi^* (U psi_+ + U^* psi_-)] = Im[psi^* NS]
+                    const float fv = rhs_node(c, ns);
+                    if (vy[r]) {
+                        (fw + pbase)[m] = fv;
+                        acc += (double)fv * (double)node_w(I, x, y0 + w * ROWS + r, k);
+                    }
+                    continue;
+                }
+                float2 nw;
+                if (is_first_mode(MODE)) {
+                    float2 bhv, dhv;
+                    float r2;
+                    const float2 zz =
+                        noise ? langevin2(I, (unsigned)k * NXY + m, nstep) : make_float2(0.f, 0.f);
+                    assemble_node(c, ep[r], u * (I.driven ? mu[r] - mu_mean : 0.f), ns, S2, ht2, noise, zz, bhv, dhv,
+                                  nw, r2);
+                    if (vy[r]) {
+                        if (NT) {
+                            st2nt(bhw + pbase, m, bhv);
+                            st2nt(dhw + pbase, m, dhv);
+                        } else {
+                            st2(bhw + pbase, m, bhv);
+                            st2(dhw + pbase, m, dhv);
+                        }
+                        // side copies for the two-sweep super-tiles (one 16-byte
+                        // global store each)
+                        if (eL >= 0) st4(I.edge, (unsigned)eL + 2u * r + eplane * k, bhv, dhv);
+                        if (eR >= 0) st4(I.edge, (unsigned)eR + 2u * r + eplane * k, bhv, dhv);
+                        rmaxb = rmax_bits(rmaxb, r2);
+                    }
+                } else {
+                    nw = jacobi(bh[r], dh[r], ns);
+                    const unsigned rb = rmax_bits(rmaxb, resid2(nw, c, dh[r], ht2));
+                    rmaxb = vy[r] ? rb : rmaxb;
+                }
+                if (vy[r]) {
+                    if (NT) st2nt(dst + pbase, m, nw);
+                    else st2(dst + pbase, m, nw);
+                }
             }
-            if (NT) st2nt(dst, m, nw);
-            else st2(dst, m, nw);
-        }
+        };
+        if (zm && zp) rows(std::true_type{});
+        else rows(std::false_type{});
+        load_streams(k + 1, k + 1 < k1, bh, dh, ep, mu);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             pm[r] = pc[r];
             pc[r] = pn[r];
-            if (k + 1 < k1) {
-                pn[r] = pnn[r];
-                bh[r] = bhn[r];
-                dh[r] = dhn[r];
-                ep[r] = epn[r];
-                mu[r] = mun[r];
-            }
         }
-        hv = hvn;
     }
+    const float rmax = __uint_as_float(rmaxb);
 
     if (MODE == MODE_NS) {
         return;

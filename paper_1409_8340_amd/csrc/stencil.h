@@ -142,6 +142,25 @@ __device__ __forceinline__ float2 fetch(const gf2 *__restrict__ src, const gf2 *
     return s.mode == SRC_P ? xcmul(ph, v) : xcmulc(ph, v);
 }
 
+// The value of slot s in plane k from its source's loaded value v: fetch()
+// in two steps, so that the load can be issued planes ahead.
+template <bool YZ>
+__device__ __forceinline__ float2 settle(const gf2 *__restrict__ P, int k, int nx, const CellSrc &s, float2 v,
+                                         const float2 *__restrict__ wz) {
+    if (s.mode == SRC_PLAIN) return v;
+    if (s.mode == SRC_ZERO) return make_float2(0.f, 0.f);
+    if (s.mode == SRC_FAC) {
+        if (YZ) {
+            float2 w2 = xcmul(wz[k], wz[k]);
+            if (s.px) w2.y = -w2.y;
+            return xcmul(xcmul(s.fac, w2), v);
+        }
+        return xcmul(s.fac, v);
+    }
+    const float2 ph = ld2(P, (unsigned)k * nx + s.px);
+    return s.mode == SRC_P ? xcmul(ph, v) : xcmulc(ph, v);
+}
+
 // Like cell_src, for slots up to two nodes outside the grid and the corners
 // of the one-node ring, as the two-sweep kernel's two-node halo needs them:
 // each axis maps on its own (periodic: wrap at any distance, the y wrap
@@ -222,6 +241,30 @@ __device__ __forceinline__ float2 nsum(float2 ux, float2 uz, float2 xm, float2 x
     const float2 yt = xcadd(yp, ym);
     return make_float2(__builtin_fmaf(cx, xt.x, __builtin_fmaf(cy, yt.x, cz * zt.x)),
                        __builtin_fmaf(cx, xt.y, __builtin_fmaf(cy, yt.y, cz * zt.y)));
+}
+
+// A value that every lane of the wavefront holds, moved to scalar registers.
+__device__ __forceinline__ float2 to_scalar(float2 v) {
+    return make_float2(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.x))),
+                       __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.y))));
+}
+
+// nsum() at a node with both z neighbours (no branch): the same operations.
+__device__ __forceinline__ float2 nsum_in(float2 ux, float2 uz, float2 xm, float2 xp, float2 ym, float2 yp,
+                                          float2 zmv, float2 zpv, float cx, float cy, float cz) {
+#pragma clang fp contract(off)
+    const float2 zt = xcadd(xcmul(uz, zpv), xcmulc(uz, zmv));
+    const float2 xt = xcadd(xcmul(ux, xp), xcmulc(ux, xm));
+    const float2 yt = xcadd(yp, ym);
+    return make_float2(__builtin_fmaf(cx, xt.x, __builtin_fmaf(cy, yt.x, cz * zt.x)),
+                       __builtin_fmaf(cx, xt.y, __builtin_fmaf(cy, yt.y, cz * zt.y)));
+}
+
+// Running maximum of |r|^2 as float bits: non-negative floats compare as
+// integers, and a NaN's bits exceed every number's, so a NaN wins.
+__device__ __forceinline__ unsigned rmax_bits(unsigned m, float r2) {
+    const unsigned b = __float_as_uint(r2);
+    return b > m ? b : m;
 }
 
 // One Jacobi iterate (Eq. final): b/M + (ht/2)/M * NS.
