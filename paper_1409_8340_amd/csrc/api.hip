@@ -972,12 +972,21 @@ void launch_sweep2(tdgl_ctx *c, int l) {
 // cooperative launch: as many work-groups as can be resident at once (a
 // multiple of 8 for the XCD-aware tile order), never more than tiles.
 // l0 = -1: lcap timing sweeps instead (state untouched).
+// Most work-groups per CU of the persistent solve (one wavefront each on the
+// CU's four SIMDs).  All of its grid has to be resident at once, and the
+// occupancy query counts a wavefront's own scalar registers only: at 112 of
+// the 800 of a SIMD (its 106 rounded up) it answers seven, but the trap
+// handler's 16 come on top of each wavefront's, so that six fit and a grid of
+// seven per CU waits at its first barrier for work-groups that never start.
+constexpr int kPersistPerCu = 800 / (112 + 16);
+
 template <int R, bool NT>
 tdgl_status launch_persist_r(tdgl_ctx *c, int l0, int lcap) {
     const void *fn = (const void *)k_jacobi_persist<R, NT>;
     int per_cu = 0;
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, WG, 0));
     if (per_cu < 1) return fail(TDGL_EDEVICE, "the persistent Jacobi kernel cannot be resident");
+    per_cu = std::min(per_cu, kPersistPerCu);
     int grid = std::min(per_cu * c->num_cu, c->tot_st);
     if (grid >= 8) grid -= grid % 8;
     grid = std::max(grid, 1);
