@@ -407,7 +407,8 @@ typedef struct tdgl_tiling {
 
 /* Picks the stencil tiling of the context by timing one Jacobi sweep for
  * each candidate (rows in {1, 2, 4} x chunk in {heuristic, 4, 8, 16, 32,
- * 64, 128, 256} up to the deepest instance's z x streaming hints off/on x
+ * 64, 128, 256} up to the deepest instance's z x streaming hints off and,
+ * where the sweep's arrays exceed the last-level cache by a quarter, on x
  * one or two sweeps per pass; the two-sweep candidates vary chunk2 and the
  * super-tile height (super_rows 16 or 32) and keep
  * the stencil chunk of the fastest single sweep with the same rows and

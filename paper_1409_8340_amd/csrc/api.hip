@@ -431,6 +431,7 @@ struct tdgl_ctx {
     int max_iter = 1, max_cycles = 1;
     int rows = 2;     // stencil rows per thread
     bool nt = false;  // streaming (non-temporal) hints in the sweep and assemble passes
+    bool big = false;      // the sweep's arrays far exceed the last-level cache
     bool fused = false;  // Jacobi sweeps after the first run as two-sweep passes
     // the last kHist sweep counts of every instance's host-driven solves
     // (0: time steps, 1: the adjoint's systems; -1 = none yet), from which
@@ -663,10 +664,18 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
         ctx->npad = npad;
         ctx->rows = ctx_rows(n, params);
         // streaming hints by default when the sweep's arrays (32 B per node)
-        // exceed the 256 MB last-level cache; tdgl_autotune measures it
+        // exceed the 256 MB last-level cache by so much that little of them
+        // is left there from one sweep to the next.  Whole runs, plain ->
+        // streamed: 256 x 256 x 64 (134 MB) 4.21 -> 4.50 ms, 320 x 256 x 90
+        // (236 MB) 7.07 -> 7.36 ms, 24 instances of 302 MB 11.33 -> 11.58 ms,
+        // 320 x 256 x 128 (335 MB) 9.98 -> 9.72 ms, 384 x 384 x 100 (472 MB)
+        // 13.42 -> 13.24 ms.  tdgl_autotune compares the two above that line
+        // only: its passes all write the same buffer, which no later one
+        // reads, so that they show the gain of a streamed store and not its
+        // price.
         double bytes = 0.0;
         for (int i = 0; i < n; ++i) bytes += 32.0 * params[i].nx * params[i].ny * params[i].nz;
-        ctx->nt = bytes > 256.0 * 1024 * 1024;
+        ctx->nt = ctx->big = bytes > 320.0 * 1024 * 1024;
         ctx->max_iter = max_iter;
         ctx->max_cycles = max_cycles;
     }
@@ -2373,6 +2382,7 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
         for (int c : chunks)
             for (int ty : {0, 16, 32}) {
                 if (c > 4 && c / 2 >= nzmax) continue;
+                if (nt && !ctx->big) continue;
                 // super-tile heights are a two-sweep notion; 32 rows need R >= 2
                 if ((fu == 0) != (ty == 0) || (ty == 32 && r == 1)) continue;
                 // the two-sweep kernels have no z-seam phase
