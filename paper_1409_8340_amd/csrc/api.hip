@@ -330,6 +330,7 @@ struct InstHost {
     int r4_blocks = 0;  // blocks of the four-row Poisson right-side pass
     float2 *edge_buf = nullptr;  // side copies of b/M for two-sweep super-tiles (Inst::edge when in use)
     int mg_blocks[kMaxLevels] = {0};
+    std::vector<int> mg_tab;  // table of the multigrid tail (MgTab)
     int fx_blocks = 0, fy_blocks = 0, fz_blocks = 0;  // spectral Poisson passes
     double Bx = 0, Bz = 0, J = 0;
     double By = 0;
@@ -427,6 +428,8 @@ struct tdgl_ctx {
     bool any_zseam = false;           // ... with By != 0 on a periodic z axis (single sweeps, no adjoint)
     bool any_fft = false, any_mg = false;
     int co_nodes = 0;  // largest coarsest multigrid level
+    int mg_tail = 0, tail_nodes = 0;  // largest first level of k_mg_tail, and its most nodes
+    size_t tail_lds = 0;              // its LDS
     bool any_driven = false;
     int max_iter = 1, max_cycles = 1;
     int rows = 2;     // stencil rows per thread
@@ -459,6 +462,56 @@ struct tdgl_ctx {
 };
 
 namespace {
+
+// Floats of LDS that k_mg_tail needs for the levels' values.
+size_t tail_floats(const Inst &d) {
+    size_t f = 0;
+    if (d.nlev == 1) return f;
+    for (int l = d.mg_tail; l < d.nlev; ++l) f += 3 * (size_t)d.lev[l].N;
+    return f;
+}
+
+// The sizes and tables of an instance's levels mg_tail - 1 .. as k_mg_tail
+// reads them (MgTab; empty for a hierarchy of one level).  At most four words
+// per node of the tail and 60 per level, so that table and values stay below
+// 120 KB of LDS: a level's axes add up to a third of its nodes and 4 at most
+// where it can be coarsened (some axis has 3 nodes or more), to half and 3 on
+// the coarsest (some axis has 2 or more), with 12 words per axis index there,
+// 8 here.
+std::vector<int> tail_table(const InstHost &h) {
+    const Inst &d = h.d;
+    std::vector<int> t;
+    if (d.nlev < 2) return t;
+    const int l0 = d.mg_tail - 1, nl = d.nlev - l0;
+    t.assign((size_t)nl * MG_TAB_HEAD, 0);
+    auto put = [&](float v) {
+        int w;
+        memcpy(&w, &v, 4);
+        t.push_back(w);
+    };
+    for (int l = l0; l < d.nlev; ++l) {
+        const LevelHost &L = h.H.lev[l];
+        MgTab e{L.n[0], L.n[1], L.n[2], (int)L.N, L.ax[0].per, L.ax[1].per, L.ax[2].per, 0, 0, 0};
+        const bool more = l + 1 < d.nlev;
+        if (l > l0) {
+            e.coef = (int)t.size();
+            for (int a = 0; a < 3; ++a) for (double v : L.ax[a].ap) put((float)v);
+            for (int a = 0; a < 3; ++a) for (double v : L.ax[a].am) put((float)v);
+            e.pro = (int)t.size();
+            if (more) {
+                for (int a = 0; a < 3; ++a) t.insert(t.end(), L.tr[a].pk.begin(), L.tr[a].pk.end());
+                for (int a = 0; a < 3; ++a) for (float v : L.tr[a].pw) put(v);
+            }
+        }
+        e.res = (int)t.size();
+        if (more) {
+            for (int a = 0; a < 3; ++a) t.insert(t.end(), L.tr[a].rk.begin(), L.tr[a].rk.end());
+            for (int a = 0; a < 3; ++a) for (float v : L.tr[a].rw) put(v);
+        }
+        memcpy(&t[(size_t)(l - l0) * MG_TAB_HEAD], &e, sizeof e);
+    }
+    return t;
+}
 
 size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
     Carver cv{base};
@@ -612,6 +665,15 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 L.tiles_z = cdiv(L.nz, L.chunk);
                 h.mg_blocks[l] = (int)(mtxy * L.tiles_z);
             }
+            // levels of k_mg_tail: the coarsest, and finer ones while they fit
+            d.mg_tail = d.nlev - 1;
+            for (long sum = d.lev[d.nlev - 1].N; d.mg_tail > 1; --d.mg_tail) {
+                sum += d.lev[d.mg_tail - 1].N;
+                if (sum > MG_TAIL_NODES) break;
+            }
+            h.mg_tab = tail_table(h);
+            d.mg_words = (int)h.mg_tab.size();
+            d.mg_tab = cv.take<int>(h.mg_tab.size());
             d.mu = d.lev[0].mu[0];
             d.f = d.lev[0].rhs;
             if (fft_eligible(p)) {
@@ -752,6 +814,8 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
     for (int i = 0; i < ctx->n; ++i) {
         InstHost &h = ctx->inst[i];
         if (!h.p.driven) continue;
+        if (!h.mg_tab.empty())
+            HIPCHK(hipMemcpy((void *)h.d.mg_tab, h.mg_tab.data(), h.mg_tab.size() * 4, hipMemcpyHostToDevice));
         for (int l = 0; l < h.d.nlev; ++l) {
             LevelHost &LH = h.H.lev[l];
             MGLevel &L = h.d.lev[l];
@@ -773,7 +837,13 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         }
     }
     for (const auto &h : ctx->inst)
-        if (h.p.driven && !h.d.fft) ctx->co_nodes = std::max(ctx->co_nodes, (int)h.H.lev.back().N);
+        if (h.p.driven && !h.d.fft) {
+            const Inst &d = h.d;
+            ctx->co_nodes = std::max(ctx->co_nodes, (int)h.H.lev.back().N);
+            ctx->mg_tail = std::max(ctx->mg_tail, d.mg_tail);
+            ctx->tail_lds = std::max(ctx->tail_lds, (d.mg_words + tail_floats(d)) * 4);
+            ctx->tail_nodes = std::max(ctx->tail_nodes, d.lev[d.mg_tail].N);
+        }
     // prefix tables
     const int n = ctx->n;
     std::vector<int> ps(n + 1, 0), pf(n + 1, 0), pm((size_t)kMaxLevels * (n + 1), 0),
@@ -790,7 +860,7 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         for (int l = 0; l < kMaxLevels; ++l) {
             const size_t o = (size_t)l * (n + 1) + i;
             const int b = (mg && l < h.d.nlev) ? h.mg_blocks[l] : 0;
-            const int bm = (mg && l + 1 < h.d.nlev) ? h.mg_blocks[l] : 0;
+            const int bm = (mg && l < h.d.mg_tail) ? h.mg_blocks[l] : 0;
             pm[o + 1] = pm[o] + b;
             pmid[o + 1] = pmid[o] + bm;
         }
@@ -854,6 +924,9 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         for (const void *fn : {(const void *)k_fft_zsolve<2>, (const void *)k_fft_zsolve<4>})
             HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ctx->fz_lds));
     }
+    for (const void *fn : {(const void *)k_mg_tail<1>, (const void *)k_mg_tail<4>})
+        if (ctx->tail_lds > 0)
+            HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ctx->tail_lds));
     HIPCHK(hipMemcpy(ctx->d_pref_st, ps.data(), (n + 1) * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_flat, pf.data(), (n + 1) * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_mg, pm.data(), pm.size() * 4, hipMemcpyHostToDevice));
@@ -1071,22 +1144,22 @@ void launch_assemble(tdgl_ctx *c, int l = 0) {
 
 // One multigrid V-cycle for every driven instance (cycle index cyc).
 // Instances may have hierarchies of different depth: each per-level launch
-// covers only the instances the operation applies to (prefix tables with
-// zero blocks for the others), and the one-group coarse solve runs every
-// instance on its own coarsest level.  Per instance and level the sequence
-// is V(2,2) with damped-Jacobi smoothing; the finest level starts a cycle
-// with its residual (the convergence test) and ends it with four sweeps.
+// covers only the instances that have the level above their tail (prefix
+// tables with zero blocks for the others), and the tail kernel runs every
+// instance on its own coarsest levels, one work-group each.  Per instance and
+// level the sequence is V(2,2) with damped-Jacobi smoothing; the finest level
+// starts a cycle with its residual (the convergence test) and ends it with
+// four sweeps.
 tdgl_status enqueue_vcycle(tdgl_ctx *c, int cyc) {
     hipStream_t s = c->stream;
     const int n = c->n;
-    const int L = c->nlev_max;
     auto grid = [](int b) { return dim3(std::max(b, 1)); };
     {
         ProfScope ps(c, TDGL_K_MG_FINE);
         hipLaunchKernelGGL(k_mg_residual, grid(c->tot_mg[0]), dim3(256), 0, s, c->d_inst, pref_mg(c, 0), n, 0,
                            0, cyc);
     }
-    for (int l = 0; l + 1 < L; ++l) {
+    for (int l = 0; l < c->mg_tail; ++l) {
         ProfScope ps(c, TDGL_K_MG_COARSE);
         if (l >= 1) {
             hipLaunchKernelGGL(k_mg_smooth, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l), n,
@@ -1094,20 +1167,20 @@ tdgl_status enqueue_vcycle(tdgl_ctx *c, int cyc) {
             hipLaunchKernelGGL(k_mg_residual, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l),
                                n, l, 1, cyc);
         }
-        // restrict into level l+1 for the instances that have it
-        hipLaunchKernelGGL(k_mg_restrict, grid(c->tot_mg[l + 1]), dim3(256), 0, s, c->d_inst,
-                           pref_mg(c, l + 1), n, l, cyc, kOmega);
+        // restrict into level l+1 for the instances whose tail starts below it
+        if (c->tot_mid[l + 1] > 0)
+            hipLaunchKernelGGL(k_mg_restrict, grid(c->tot_mid[l + 1]), dim3(256), 0, s, c->d_inst,
+                               pref_mid(c, l + 1), n, l, cyc, kOmega);
     }
     {
         ProfScope ps(c, TDGL_K_MG_COARSE);
-        const dim3 th(std::min(CO_THREADS, (c->co_nodes + 63) / 64 * 64));
-        const size_t lds = (size_t)2 * c->co_nodes * sizeof(float);
+        const dim3 th(std::min(CO_THREADS, (std::max(c->co_nodes, c->tail_nodes) + 63) / 64 * 64));
         if (c->co_nodes <= CO_THREADS)
-            hipLaunchKernelGGL(k_mg_coarsest<1>, dim3(n), th, lds, s, c->d_inst, n, cyc);
+            hipLaunchKernelGGL(k_mg_tail<1>, dim3(n), th, c->tail_lds, s, c->d_inst, n, cyc, kOmega);
         else
-            hipLaunchKernelGGL(k_mg_coarsest<4>, dim3(n), th, lds, s, c->d_inst, n, cyc);
+            hipLaunchKernelGGL(k_mg_tail<4>, dim3(n), th, c->tail_lds, s, c->d_inst, n, cyc, kOmega);
     }
-    for (int l = L - 2; l >= 0; --l) {
+    for (int l = c->mg_tail - 1; l >= 0; --l) {
         ProfScope ps(c, l == 0 ? TDGL_K_MG_FINE : TDGL_K_MG_COARSE);
         const int ifine = (l == 0) ? 0 : 1;
         hipLaunchKernelGGL(k_mg_prolong, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l), n, l,

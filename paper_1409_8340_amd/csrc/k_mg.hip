@@ -21,6 +21,8 @@
 #include "kernels.h"
 #include "stencil.h"
 
+#include <type_traits>
+
 namespace tdgl {
 
 struct MGCols {
@@ -250,39 +252,37 @@ __global__ __launch_bounds__(256) void k_mg_prolong(const Inst *__restrict__ ins
     }
 }
 
-// Coarsest level: one work-group per instance iterates Jacobi sweeps in
-// double precision on an FP32 iterate until the residual falls below 1e-6 of
-// the right side or 4000 sweeps, after projecting the right side onto the
-// range (zero volume-weighted mean) and shifting the result to zero mean.
-// Result in mu[0].  The level may be the finest one (tiny grids): then its
-// right side is f minus its weighted mean and the iterate starts from the
-// stored mu.
-// The iterate sits in LDS (two buffers of N floats), a thread keeps its
-// nodes' coefficients and right sides in registers, and a sweep ends at one
-// barrier with a vote on the residual, since only whether the maximum exceeds
-// the threshold matters.  Through global memory, with the maximum reduced
+// Coarsest level L of a work-group: Jacobi sweeps in double precision on an
+// FP32 iterate until the residual falls below 1e-6 of the right side or 4000
+// sweeps, after projecting the right side rhs - fm onto the range (zero
+// volume-weighted mean).  Starts from mu0, or from zero without one; returns
+// the LDS buffer with the result and the mean to subtract.
+// A thread keeps its nodes' coefficients and right sides in registers, and a
+// sweep ends at one barrier with a vote on the residual, since only whether
+// the maximum exceeds the threshold matters.  A sweep is a chain of some 20
+// FP64 operations between two LDS round trips, so everything else is kept out
+// of it: the vote of a sweep is read with the next sweep's loads (that sweep
+// is dropped before it stores when the vote has closed the iteration), buffers
+// and words have fixed addresses over six unrolled sweeps, and threads without
+// a node sweep a slot of their own under an infinite threshold.  Through global memory, with the maximum reduced
 // every sweep over 1024 threads, a solve took 465 us on average on the 12 x 8
-// x 3 nodes below 192 x 101 x 33, three quarters of that box's step.  The
-// values are those of that form, bit for bit: the quotient by D is its
-// reciprocal's product corrected once with the exact remainder, which rounds
-// as the division does (Markstein, IBM J. Res. Dev. 34, 1990).  (A direct
-// solve through the axes' modes takes 7 us, but what it takes away from the
-// stop rule's error reaches the ninth digit of K.)
+// x 3 nodes below 192 x 101 x 33, three quarters of that box's step, and 87 us
+// with the vote read behind its own barrier and addresses made per sweep.  The values are those of that
+// form, bit for bit: the quotient by D is its reciprocal's product corrected
+// once with the exact remainder, which rounds as the division does (Markstein,
+// IBM J. Res. Dev. 34, 1990).  (A direct solve through the axes' modes takes
+// 7 us, but what it takes away from the stop rule's error reaches the ninth
+// digit of K.)
 // NPT: nodes per thread (1 where N fits the work-group, else 4).
 template <int NPT>
-__global__ __launch_bounds__(CO_THREADS) void k_mg_coarsest(const Inst *__restrict__ insts,
-                                                            int ninst, int cyc) {
-    extern __shared__ float co_sm[];
+__device__ __forceinline__ const float *mg_coarsest(const MGLevel &L, const float *rhs, double fm, const float *mu0,
+                                                    float &mmean) {
+    constexpr int CAP = NPT * CO_THREADS;
+    __shared__ float cb[2][CAP];
     __shared__ double red[CO_THREADS / 64];
     __shared__ double sh_v;
     __shared__ int open[3];
-    const Inst &I = insts[blockIdx.x];
-    if (!I.driven || I.fft || mg_done(I, cyc)) return;
-    const int lv = I.nlev - 1;
-    const MGLevel &L = I.lev[lv];
     const int N = L.N, nt = (int)blockDim.x, nw = nt >> 6;
-    const double fm = (lv == 0) ? I.st->f_mean : 0.0;
-    float *a = co_sm, *bq = co_sm + N;
     auto sum = [&](double v) {
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
         __syncthreads();
@@ -309,7 +309,8 @@ __global__ __launch_bounds__(CO_THREADS) void k_mg_coarsest(const Inst *__restri
         at[i][3] = z * nxy + ym * nx + x;
         at[i][4] = zp * nxy + y * nx + x;
         at[i][5] = zm * nxy + y * nx + x;
-        at[i][6] = mm;
+        at[i][6] = m;
+        cb[0][m] = mu0 && m < N ? mu0[m] : 0.f;
         co[i][0] = (double)L.ap[0][x];
         co[i][1] = (double)L.am[0][x];
         co[i][2] = (double)L.ap[1][y];
@@ -319,10 +320,9 @@ __global__ __launch_bounds__(CO_THREADS) void k_mg_coarsest(const Inst *__restri
         D[i] = -((double)L.ap[0][x] + L.am[0][x] + L.ap[1][y] + L.am[1][y] + L.ap[2][z] + L.am[2][z]);
         rD[i] = D[i] != 0.0 ? 1.0 / D[i] : 0.0;  // 0: the node keeps its value
         V[i] = (double)L.vol[0][x] * L.vol[1][y] * L.vol[2][z];
-        d0[i] = (double)L.rhs[mm] - fm;
+        d0[i] = (double)rhs[mm] - fm;
         // volume-weighted mean of the right side
         if (m < N) s += V[i] * d0[i];
-        if (m < N) a[m] = lv != 0 ? 0.f : L.mu[0][m];
     }
     if (threadIdx.x < 3) open[threadIdx.x] = 0;
     s = sum(s);
@@ -343,49 +343,256 @@ __global__ __launch_bounds__(CO_THREADS) void k_mg_coarsest(const Inst *__restri
         sh_v = mx;
     }
     __syncthreads();
-    const double thr = 1e-6 * sh_v;
-    int ph = 0;  // sweep index mod 3
-    for (int it = 0; it < 4000; ++it) {
-        bool over = false;
+    double thr[NPT];
 #pragma unroll
-        for (int i = 0; i < NPT; ++i) {
-            const double mc = a[at[i][6]];
-            const double Amu = co[i][0] * (a[at[i][0]] - mc) + co[i][1] * (a[at[i][1]] - mc) +
-                               co[i][2] * (a[at[i][2]] - mc) + co[i][3] * (a[at[i][3]] - mc) +
-                               co[i][4] * (a[at[i][4]] - mc) + co[i][5] * (a[at[i][5]] - mc);
-            const double r = d0[i] - Amu;
-            const double x = 0.9 * r, q = x * rD[i];
-            const double quo = __builtin_fma(__builtin_fma(-q, D[i], x), rD[i], q);
-            if ((int)threadIdx.x + i * nt < N) {
-                over = over || fabs(r) > thr;
-                bq[at[i][6]] = (rD[i] != 0.0) ? (float)(mc + quo) : (float)mc;
+    for (int i = 0; i < NPT; ++i)
+        thr[i] = (int)threadIdx.x + i * nt < N ? 1e-6 * sh_v : (double)INFINITY;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool busy = w * 64 < N;  // some node of the wavefront's is one of the level's
+    // sweep it = J mod 6 from cb[J & 1]; false: the sweep before ended the
+    // iteration (its result is in cb[J & 1])
+    auto sweep = [&](auto jc, int it) __attribute__((always_inline)) {
+        constexpr int J = decltype(jc)::value, ph = J % 3, pq = (ph + 2) % 3, pn = (ph + 1) % 3;
+        const float *a = cb[J & 1];
+        float *bq = cb[(J & 1) ^ 1];
+        const int going = open[pq];  // the vote of the sweep before
+        float nv[NPT];
+        bool over = false;
+        if (busy) {
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+                const double mc = a[at[i][6]];
+                const double Amu = co[i][0] * (a[at[i][0]] - mc) + co[i][1] * (a[at[i][1]] - mc) +
+                                   co[i][2] * (a[at[i][2]] - mc) + co[i][3] * (a[at[i][3]] - mc) +
+                                   co[i][4] * (a[at[i][4]] - mc) + co[i][5] * (a[at[i][5]] - mc);
+                const double r = d0[i] - Amu;
+                const double x = 0.9 * r, q = x * rD[i];
+                const double quo = __builtin_fma(__builtin_fma(-q, D[i], x), rD[i], q);
+                over = over || fabs(r) > thr[i];
+                nv[i] = (rD[i] != 0.0) ? (float)(mc + quo) : (float)mc;
             }
         }
-        if (__ballot(over) != 0 && (threadIdx.x & 63) == 0) open[ph] = 1;
+        if (it > 0 && !__builtin_amdgcn_readfirstlane(going)) return false;
+        if (busy) {
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) bq[at[i][6]] = nv[i];
+            if (__ballot(over) != 0) open[ph] = 1;
+        }
+        // the next sweep's word: read last in the sweep before this one
+        if (w == 0) open[pn] = 0;
         __syncthreads();
-        // swap roles
-        float *t = a;
-        a = bq;
-        bq = t;
-        if (!open[ph]) break;
-        // the word of the sweep after next: its last readers passed this barrier
-        const int p2 = ph == 0 ? 2 : ph - 1;
-        if (threadIdx.x == 0) open[p2] = 0;
-        ph = ph == 2 ? 0 : ph + 1;
+        return true;
+    };
+    int ph = 0;  // the buffer with the result
+    for (int it = 0; it < 4000; ++it) {
+        ph = 0;
+        if (!sweep(std::integral_constant<int, 0>{}, it)) break;
+        ph = 1;
+        if (++it >= 4000 || !sweep(std::integral_constant<int, 1>{}, it)) break;
+        ph = 0;
+        if (++it >= 4000 || !sweep(std::integral_constant<int, 2>{}, it)) break;
+        ph = 1;
+        if (++it >= 4000 || !sweep(std::integral_constant<int, 3>{}, it)) break;
+        ph = 0;
+        if (++it >= 4000 || !sweep(std::integral_constant<int, 4>{}, it)) break;
+        ph = 1;
+        if (++it >= 4000 || !sweep(std::integral_constant<int, 5>{}, it)) break;
+        ph = 0;
     }
-    // shift to zero weighted mean and leave the result in mu[0]
+    float *a = cb[ph];
+    // shift to zero weighted mean
     double sm = 0.0;
 #pragma unroll
     for (int i = 0; i < NPT; ++i)
         if ((int)threadIdx.x + i * nt < N) sm += V[i] * a[at[i][6]];
     sm = sum(sm);
-    const float mmean = (float)(sm / L.vsum);
-#pragma unroll
-    for (int i = 0; i < NPT; ++i)
-        if ((int)threadIdx.x + i * nt < N) L.mu[0][at[i][6]] = a[at[i][6]] - mmean;
+    mmean = (float)(sm / L.vsum);
+    return a;
 }
-template __global__ void k_mg_coarsest<1>(const Inst *, int, int);
-template __global__ void k_mg_coarsest<4>(const Inst *, int, int);
+
+// The coarse end of a V-cycle in one work-group per instance: levels
+// I.mg_tail and coarser, from the restriction of the next finer level's
+// residual to the correction of level I.mg_tail, with the iterates and right
+// sides in LDS (the residual takes the place of the level's first iterate,
+// which the smoothing has used up).  The operations and their order are those
+// of the per-level kernels, so are the bits.  A launch of these levels' kernels
+// takes 5 to 7 us, whatever its size; here an operation takes one barrier.
+// The levels' tables come to LDS in one piece, since a chain of pointer, table
+// and value loads costs an operation as much as a launch does.
+// A hierarchy of one level (tiny grids) is solved directly: its right side is
+// f minus its weighted mean and the iterate starts from the stored mu.
+// 192 x 101 x 33 nodes (tail 24 x 14 x 5 and 12 x 8 x 3), per V-cycle: 78 us,
+// nearly all of it the coarsest level's sweeps, for seven launches of 125 us;
+// a run of six steps 11.6 -> 10.2 ms.
+template <int NPT>
+__global__ __launch_bounds__(CO_THREADS) void k_mg_tail(const Inst *__restrict__ insts, int ninst, int cyc,
+                                                        float omega) {
+    extern __shared__ float tail_sm[];
+    const Inst &I = insts[blockIdx.x];
+    if (!I.driven || I.fft || mg_done(I, cyc)) return;
+    const int last = I.nlev - 1, lt = I.mg_tail, nt = (int)blockDim.x;
+    // the levels' sizes and tables, from level lt - 1 on (see MgTab), then 3 N
+    // floats per level: its iterates and right side
+    int *tab = (int *)tail_sm;
+    for (int i = threadIdx.x; i < I.mg_words; i += nt) tab[i] = I.mg_tab[i];
+    const float *ftab = (const float *)tail_sm;
+    auto lev = [&](int l) {
+        MgTab v;
+        const int *h = tab + (l - lt + 1) * MG_TAB_HEAD;
+        int w[MG_TAB_HEAD];
+#pragma unroll
+        for (int i = 0; i < MG_TAB_HEAD; ++i) w[i] = __builtin_amdgcn_readfirstlane(h[i]);
+        v.nx = w[0]; v.ny = w[1]; v.nz = w[2]; v.N = w[3];
+        v.px = w[4]; v.py = w[5]; v.pz = w[6];
+        v.coef = w[7]; v.pro = w[8]; v.res = w[9];
+        return v;
+    };
+    auto restrict_to = [&](const MgTab &F, const MgTab &C, const float *r, float *rhs, float *mu0) {
+        const int Sc = C.nx + C.ny + C.nz, fnx = F.nx, fnxy = F.nx * F.ny;
+        for (int m = threadIdx.x; m < C.N; m += nt) {
+            const int x = m % C.nx, yk = m / C.nx, y = yk % C.ny, K = yk / C.ny;
+            const int o[3] = {F.res + 3 * x, F.res + 3 * (C.nx + y), F.res + 3 * (C.nx + C.ny + K)};
+            int f[3][3];
+            float w[3][3];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    f[ax][q] = tab[o[ax] + q];
+                    w[ax][q] = ftab[o[ax] + 3 * Sc + q];
+                }
+            float v[27];
+#pragma unroll
+            for (int q = 0; q < 27; ++q) v[q] = r[f[2][q / 9] * fnxy + f[1][q / 3 % 3] * fnx + f[0][q % 3]];
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < 27; ++q) {
+                const float wzy = w[2][q / 9] * w[1][q / 3 % 3];
+                s += wzy * w[0][q % 3] * v[q];
+            }
+            rhs[m] = s;
+            const float *ap = ftab + C.coef, *am = ap + Sc;
+            const float Dxy = ap[x] + am[x] + ap[C.nx + y] + am[C.nx + y];
+            const float D = -(Dxy + ap[C.nx + C.ny + K] + am[C.nx + C.ny + K]);
+            mu0[m] = (D != 0.f) ? omega * s / D : 0.f;
+        }
+    };
+    // node m of a level: its coefficients and neighbours
+    struct Node {
+        float apx, amx, apy, amy, apz, amz;
+        int xm, xp, ym, yp, zm, zp;
+    };
+    auto node = [&](const MgTab &L, int m) {
+        Node c;
+        const int nx = L.nx, nxy = L.nx * L.ny, S = L.nx + L.ny + L.nz;
+        const int x = m % nx, yk = m / nx, y = yk % L.ny, k = yk / L.ny;
+        const float *ap = ftab + L.coef, *am = ap + S;
+        c.apx = ap[x];
+        c.amx = am[x];
+        c.apy = ap[nx + y];
+        c.amy = am[nx + y];
+        c.apz = ap[nx + L.ny + k];
+        c.amz = am[nx + L.ny + k];
+        c.xm = m - x + wrapi(x - 1, nx, L.px);
+        c.xp = m - x + wrapi(x + 1, nx, L.px);
+        c.ym = m + (wrapi(y - 1, L.ny, L.py) - y) * nx;
+        c.yp = m + (wrapi(y + 1, L.ny, L.py) - y) * nx;
+        c.zm = m + (wrapi(k - 1, L.nz, L.pz) - k) * nxy;
+        c.zp = m + (wrapi(k + 1, L.nz, L.pz) - k) * nxy;
+        return c;
+    };
+    auto smooth = [&](const MgTab &L, const float *src, float *dst, const float *rhsp) {
+        for (int m = threadIdx.x; m < L.N; m += nt) {
+            const Node c = node(L, m);
+            const float mc = src[m];
+            const float Amu = c.apx * (src[c.xp] - mc) + c.amx * (src[c.xm] - mc) + c.apy * (src[c.yp] - mc) +
+                              c.amy * (src[c.ym] - mc) + c.apz * (src[c.zp] - mc) + c.amz * (src[c.zm] - mc);
+            const float D = -(c.apx + c.amx + c.apy + c.amy + c.apz + c.amz);
+            const float rhs = rhsp[m];
+            dst[m] = (D != 0.f) ? mc + omega * (rhs - Amu) / D : mc;
+        }
+    };
+    auto residual = [&](const MgTab &L, const float *src, float *r, const float *rhsp) {
+        for (int m = threadIdx.x; m < L.N; m += nt) {
+            const Node c = node(L, m);
+            const double mc = src[m];
+            const double Amu = (double)c.apx * ((double)src[c.xp] - mc) + (double)c.amx * ((double)src[c.xm] - mc) +
+                               (double)c.apy * ((double)src[c.yp] - mc) + (double)c.amy * ((double)src[c.ym] - mc) +
+                               (double)c.apz * ((double)src[c.zp] - mc) + (double)c.amz * ((double)src[c.zm] - mc);
+            r[m] = (float)((double)rhsp[m] - Amu);
+        }
+    };
+    auto prolong = [&](const MgTab &F, const MgTab &C, const float *ec, float *mf) {
+        const int cnx = C.nx, cnxy = C.nx * C.ny, nx = F.nx, S2 = 2 * (F.nx + F.ny + F.nz);
+        for (int m = threadIdx.x; m < F.N; m += nt) {
+            const int x = m % nx, yk = m / nx, y = yk % F.ny, k = yk / F.ny;
+            const int ox = F.pro + 2 * x, oy = F.pro + 2 * (nx + y), oz = F.pro + 2 * (nx + F.ny + k);
+            const int kx0 = tab[ox], kx1 = tab[ox + 1], ky0 = tab[oy], ky1 = tab[oy + 1];
+            const float wx0 = ftab[ox + S2], wx1 = ftab[ox + S2 + 1];
+            const float wy0 = ftab[oy + S2], wy1 = ftab[oy + S2 + 1];
+            const float wz0 = ftab[oz + S2], wz1 = ftab[oz + S2 + 1];
+            const int b0 = tab[oz] * cnxy, b1 = tab[oz + 1] * cnxy;
+            const float e = wz0 * (wy0 * (wx0 * ec[b0 + ky0 * cnx + kx0] + wx1 * ec[b0 + ky0 * cnx + kx1]) +
+                                   wy1 * (wx0 * ec[b0 + ky1 * cnx + kx0] + wx1 * ec[b0 + ky1 * cnx + kx1])) +
+                            wz1 * (wy0 * (wx0 * ec[b1 + ky0 * cnx + kx0] + wx1 * ec[b1 + ky0 * cnx + kx1]) +
+                                   wy1 * (wx0 * ec[b1 + ky1 * cnx + kx0] + wx1 * ec[b1 + ky1 * cnx + kx1]));
+            mf[m] += e;
+        }
+    };
+
+    const MGLevel &T = I.lev[last];
+    float mmean;
+    if (last == 0) {
+        const float *a = mg_coarsest<NPT>(T, T.rhs, I.st->f_mean, T.mu[0], mmean);
+        for (int m = threadIdx.x; m < T.N; m += nt) T.mu[0][m] = a[m] - mmean;
+        return;
+    }
+    // down
+    __syncthreads();
+    float *base = tail_sm + I.mg_words;
+    {
+        const MgTab C = lev(lt);
+        restrict_to(lev(lt - 1), C, I.lev[lt - 1].r, base + 2 * C.N, base);
+    }
+    __syncthreads();
+    for (int l = lt; l < last; ++l) {
+        const MgTab L = lev(l), C = lev(l + 1);
+        float *m0 = base, *m1 = base + L.N, *rh = base + 2 * L.N, *next = base + 3 * L.N;
+        smooth(L, m0, m1, rh);
+        __syncthreads();
+        residual(L, m1, m0, rh);
+        __syncthreads();
+        restrict_to(L, C, m0, next + 2 * C.N, next);
+        __syncthreads();
+        base = next;
+    }
+    // coarsest
+    const float *a = mg_coarsest<NPT>(T, base + 2 * T.N, 0.0, nullptr, mmean);
+    if (lt == last) {
+        for (int m = threadIdx.x; m < T.N; m += nt) T.mu[0][m] = a[m] - mmean;
+        return;
+    }
+    float *e = base;
+    for (int m = threadIdx.x; m < T.N; m += nt) e[m] = a[m] - mmean;
+    __syncthreads();
+    // up
+    for (int l = last - 1; l >= lt; --l) {
+        const MgTab L = lev(l);
+        base -= 3 * L.N;
+        float *m0 = base, *m1 = base + L.N, *rh = base + 2 * L.N;
+        prolong(L, lev(l + 1), e, m1);
+        __syncthreads();
+        smooth(L, m1, m0, rh);
+        __syncthreads();
+        smooth(L, m0, m1, rh);
+        __syncthreads();
+        e = m1;
+    }
+    const MGLevel &L = I.lev[lt];
+    for (int m = threadIdx.x; m < L.N; m += nt) L.mu[1][m] = e[m];
+}
+template __global__ void k_mg_tail<1>(const Inst *, int, int, float);
+template __global__ void k_mg_tail<4>(const Inst *, int, int, float);
 
 // End of a Poisson solve: number of cycles and final residual; clears the
 // cycle words.  One thread per instance.

@@ -11,6 +11,11 @@ constexpr bool is_first_mode(int m) { return m == MODE_FIRST || m == MODE_FIRSTN
 constexpr int JAV_CPT = 16;     // least cells per thread of the flat reductions (a multiple of 8)
 constexpr int JAV_CPT_MAX = 64; // most cells per thread, taken while 2048 or more work-groups remain
 constexpr int CO_THREADS = 1024;
+// Most nodes of the levels that k_mg_tail takes, 12 bytes of LDS each: one CU's
+// work per level against launches of 5 us.  Whole runs of 192 x 101 x 33 with
+// the tail at 12 x 8 x 3 alone / from 24 x 14 x 5 (1968 nodes) / from 48 x 26 x
+// 9 (13200): 11.9 / 11.5 / 14.3 ms.
+constexpr int MG_TAIL_NODES = 4096;
 constexpr int FIN_THREADS = 256;  // threads per instance of the solve finalizers
 
 template <int R, bool NT, bool YZ>
@@ -65,7 +70,7 @@ __global__ void k_mg_restrict(const Inst *insts, const int *prefix, int ninst, i
 __global__ void k_mg_prolong(const Inst *insts, const int *prefix, int ninst, int lv, int ifine,
                              int cyc);
 template <int NPT>
-__global__ void k_mg_coarsest(const Inst *insts, int ninst, int cyc);
+__global__ void k_mg_tail(const Inst *insts, int ninst, int cyc, float omega);
 __global__ void k_mg_finalize(const Inst *insts, int ninst, int count_step);
 __global__ void k_mu_mean_partial(const Inst *insts, const int *prefix, int ninst, int which);
 

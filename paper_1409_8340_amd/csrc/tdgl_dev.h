@@ -94,6 +94,16 @@ struct MGLevel {
     int tiles_x, tiles_y, tiles_z, chunk;
 };
 
+// A level of k_mg_tail: sizes, periodic axes and the offsets (words of the
+// instance's table) of its coefficients (ap of the three axes, then am), its
+// prolongation (pk of the axes, two each, then pw) and the restriction to the
+// next coarser level (rk of that level's axes, three each, then rw).
+struct MgTab {
+    int nx, ny, nz, N, px, py, pz;
+    int coef, pro, res;
+};
+constexpr int MG_TAB_HEAD = 10;  // words of a level's entry at the table's start
+
 struct Inst {
     int nx, ny, nz, N;
     int per[3];          // 1: periodic axis, 0: open
@@ -156,6 +166,9 @@ struct Inst {
     unsigned edge_r, edge_ob, edge_od;
                          // (periodic y, ny a multiple of the super-tile height); else they start one tile row in
     int nlev;
+    int mg_tail;         // coarsest levels from here on in one work-group (k_mg_tail)
+    int mg_words;        // words of their table, from level mg_tail - 1 on
+    const int *mg_tab;
     MGLevel lev[kMaxLevels];
     // direct spectral Poisson solve (periodic x and y, open z)
     int fft;             // 1: the Poisson equation is solved by FFT, 0: by multigrid
