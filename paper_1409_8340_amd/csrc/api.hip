@@ -980,23 +980,23 @@ struct ProfScope {
 // Launch one stencil pass over every instance with the context's tile
 // (rows per thread; streaming hints for the sweep and assemble passes).
 template <int MODE, int R>
-void launch_stencil_r(tdgl_ctx *c, int l, const float2 *in, float2 *out) {
+void launch_stencil_r(tdgl_ctx *c, int l) {
     constexpr bool can_nt = (MODE == MODE_SWEEP || is_first_mode(MODE));
     unsigned long long *pub = (MODE == MODE_SWEEP && c->pub_on && l > 0) ? c->d_pub : nullptr;
     // a yz-plane field takes the variant with per-plane x links
     if (c->any_yz) {
         if (can_nt && c->nt)
             hipLaunchKernelGGL((k_stencil<MODE, R, can_nt, true>), dim3(c->tot_st), dim3(WG), 0, c->stream,
-                               c->d_inst, c->d_pref_st, c->n, l, in, out, pub, c->pub_seq);
+                               c->d_inst, c->d_pref_st, c->n, l, pub, c->pub_seq);
         else
             hipLaunchKernelGGL((k_stencil<MODE, R, false, true>), dim3(c->tot_st), dim3(WG), 0, c->stream,
-                               c->d_inst, c->d_pref_st, c->n, l, in, out, pub, c->pub_seq);
+                               c->d_inst, c->d_pref_st, c->n, l, pub, c->pub_seq);
     } else if (can_nt && c->nt) {
         hipLaunchKernelGGL((k_stencil<MODE, R, can_nt, false>), dim3(c->tot_st), dim3(WG), 0, c->stream, c->d_inst,
-                           c->d_pref_st, c->n, l, in, out, pub, c->pub_seq);
+                           c->d_pref_st, c->n, l, pub, c->pub_seq);
     } else {
         hipLaunchKernelGGL((k_stencil<MODE, R, false, false>), dim3(c->tot_st), dim3(WG), 0, c->stream, c->d_inst,
-                           c->d_pref_st, c->n, l, in, out, pub, c->pub_seq);
+                           c->d_pref_st, c->n, l, pub, c->pub_seq);
     }
 }
 template <int R, bool NT, bool YZ>
@@ -1088,10 +1088,10 @@ tdgl_status launch_persist(tdgl_ctx *c, int l0, int lcap) {
 }
 
 template <int MODE>
-void launch_stencil(tdgl_ctx *c, int l, const float2 *in = nullptr, float2 *out = nullptr) {
-    if (c->rows == 1) launch_stencil_r<MODE, 1>(c, l, in, out);
-    else if (c->rows == 2) launch_stencil_r<MODE, 2>(c, l, in, out);
-    else launch_stencil_r<MODE, 4>(c, l, in, out);
+void launch_stencil(tdgl_ctx *c, int l) {
+    if (c->rows == 1) launch_stencil_r<MODE, 1>(c, l);
+    else if (c->rows == 2) launch_stencil_r<MODE, 2>(c, l);
+    else launch_stencil_r<MODE, 4>(c, l);
 }
 // The Poisson right-side pass: with the context's tile, or on 64 x 16
 // tiles with four rows per thread (its own block table) when the tiling
@@ -1103,10 +1103,10 @@ void launch_rhs(tdgl_ctx *c) {
     }
     if (c->any_yz)
         hipLaunchKernelGGL((k_stencil<MODE_RHS, 4, false, true>), dim3(c->tot_r4), dim3(WG), 0, c->stream,
-                           c->d_inst, c->d_pref_r4, c->n, 0, nullptr, nullptr, nullptr, 0u);
+                           c->d_inst, c->d_pref_r4, c->n, 0, nullptr, 0u);
     else
         hipLaunchKernelGGL((k_stencil<MODE_RHS, 4, false, false>), dim3(c->tot_r4), dim3(WG), 0, c->stream,
-                           c->d_inst, c->d_pref_r4, c->n, 0, nullptr, nullptr, nullptr, 0u);
+                           c->d_inst, c->d_pref_r4, c->n, 0, nullptr, 0u);
 }
 
 // Per-instance counts of the partial sums the right-side pass writes.
@@ -1440,8 +1440,8 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
 // host one cycle behind.  Statistics are accumulated into acc.
 // The passes of the spectral solve for every instance that uses it: three
 // with the fused y and z pass, five otherwise.  step: the right side of a time
-// step, from psi; else the stored I.f.  Leaves the partials of the mean of mu.
-tdgl_status enqueue_fft(tdgl_ctx *ctx, bool step) {
+// step, from psi; else f, or the stored I.f without one.  Leaves the partials of the mean of mu.
+tdgl_status enqueue_fft(tdgl_ctx *ctx, bool step, const float *f = nullptr) {
     if (!ctx->any_fft) return TDGL_OK;
     const int n = ctx->n;
     hipStream_t s = ctx->stream;
@@ -1450,7 +1450,7 @@ tdgl_status enqueue_fft(tdgl_ctx *ctx, bool step) {
     const Inst *ins = ctx->d_inst;
     const int *pref = ctx->d_pref_fx;
     int nn = n;
-    const float *in = nullptr;
+    const float *in = f;
     const int src = !step || !ctx->fft_yz ? SRC_F : (ctx->any_yz ? SRC_PSI_YZ : SRC_PSI);
     {
         void *args[] = {(void *)&ins, (void *)&pref, (void *)&nn, (void *)&in};
@@ -1519,11 +1519,11 @@ void enqueue_rhs(tdgl_ctx *ctx) {
         hipLaunchKernelGGL(k_reduce_to_state, dim3(ctx->n), dim3(256), 0, ctx->stream, ctx->d_inst, rhs_parts(ctx), 0, 2);
 }
 
-tdgl_status enqueue_poisson(tdgl_ctx *ctx, tdgl_step_stats *acc, bool step) {
+tdgl_status enqueue_poisson(tdgl_ctx *ctx, tdgl_step_stats *acc, bool step, const float *f = nullptr) {
     const int n = ctx->n;
     hipStream_t s = ctx->stream;
     const size_t RW = ctx->row_words();
-    tdgl_status fe = enqueue_fft(ctx, step);
+    tdgl_status fe = enqueue_fft(ctx, step, f);
     if (fe) return fe;
     std::vector<int> mconv_at(n, 0);
     if (ctx->any_mg) {
@@ -1758,7 +1758,7 @@ tdgl_status tdgl_create(int n, const tdgl_params *params, void *ws, size_t ws_by
     hipLaunchKernelGGL(k_fill_u, dim3(64), dim3(256), 0, st, c->d_res, (long)(c->max_iter * c->row_words()), 0u);
     hipLaunchKernelGGL(k_fill_u, dim3(64), dim3(256), 0, st, c->d_mures, (long)(c->max_cycles * c->row_words()),
                        0u);
-    hipLaunchKernelGGL(k_links, dim3(n), dim3(256), 0, st, c->d_inst, 0, (const double *)nullptr);
+    hipLaunchKernelGGL(k_links, dim3(n), dim3(256), 0, st, c->d_inst, 0);
     for (int i = 0; i < n; ++i) {
         const tdgl_params &p = c->inst[i].p;
         if (!c->inst[i].d.fft) continue;
@@ -1851,7 +1851,7 @@ tdgl_status tdgl_set_field_yz(tdgl_ctx *ctx, int inst, double By, double Bz, int
     hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 9, qz);
     hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 13, qy);
     hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 14, 1.0);
-    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, ctx->stream, ctx->d_inst + inst, 0, (const double *)nullptr);
+    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, ctx->stream, ctx->d_inst + inst, 0);
     LAUNCHCHK();
     if (By_eff) *By_eff = qy;
     if (Bz_eff) *Bz_eff = qz;
@@ -1885,7 +1885,7 @@ tdgl_status tdgl_set_field(tdgl_ctx *ctx, int inst, double Bx, double Bz, int qu
     hipLaunchKernelGGL(k_state_set, dim3(1), dim3(1), 0, ctx->stream, ctx->d_inst, inst, 14, 0.0);
     // rebuild the tables of this instance only: launch over all with a
     // single-instance view (the kernel reads the descriptor by block index)
-    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, ctx->stream, ctx->d_inst + inst, 0, (const double *)nullptr);
+    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, ctx->stream, ctx->d_inst + inst, 0);
     LAUNCHCHK();
     if (Bx_eff) *Bx_eff = qx;
     if (Bz_eff) *Bz_eff = qz;
@@ -2672,14 +2672,14 @@ tdgl_status tdgl_get_tiling(const tdgl_ctx *ctx, int inst, tdgl_tiling *out) {
 namespace {
 
 struct AdjLayout {
-    float2 *ck_psi, *seg_psi, *fin_psi, *psibar, *t1, *t2, *t3, *lamW, *lamW2;
-    float *ck_mu, *seg_mu, *fin_mu, *mubar;
-    double *ck_K, *seg_K, *fin_K, *Elog, *vbar;
+    float2 *ck_psi, *seg_psi, *fin_psi, *psibar, *lamW, *lamW2, *uxn;
+    float *ck_mu, *seg_mu, *fin_mu, *f;
+    double *ck_K, *seg_K, *fin_K, *Elog, *vbar, *part;
     DevState *fin_st;
     AdjState *adj;
 };
 
-size_t adj_layout(long N, int nsteps, int C, char *base, AdjLayout *L) {
+size_t adj_layout(long N, int ny, int nsteps, int C, char *base, AdjLayout *L) {
     Carver cv{base};
     const int ncp = (nsteps + C - 1) / C;
     AdjLayout l;
@@ -2694,10 +2694,9 @@ size_t adj_layout(long N, int nsteps, int C, char *base, AdjLayout *L) {
     l.fin_K = cv.take<double>(3);
     l.fin_st = cv.take<DevState>(1);
     l.psibar = cv.take<float2>(N);
-    l.mubar = cv.take<float>(N);
-    l.t1 = cv.take<float2>(N);
-    l.t2 = cv.take<float2>(N);
-    l.t3 = cv.take<float2>(N);
+    l.f = cv.take<float>(N);
+    l.uxn = cv.take<float2>(ny);
+    l.part = cv.take<double>(4 * ADJ_GROUPS);
     l.lamW = cv.take<float2>(N);
     l.lamW2 = cv.take<float2>(N);
     l.Elog = cv.take<double>(nsteps);
@@ -2707,53 +2706,50 @@ size_t adj_layout(long N, int nsteps, int C, char *base, AdjLayout *L) {
     return cv.off;
 }
 
+// Work-groups of the adjoint's flat passes.
+int adj_groups(long N) { return std::max(1, std::min(cdiv(N, 256L), ADJ_GROUPS)); }
+
 // Reverse of one step: prev = state n-1, nxt = state n (segment slots).
 // k: reverse steps done before this one.  The last two reverse steps'
 // solutions (lambda / W) alternate between lamW and lamW2: the newest warm
 // starts this step's M^H solve (extrapolated with the older from the third
-// reverse step on), and this step's solution replaces the older.
+// reverse step on), and this step's solution replaces the older.  The sum
+// that closes a step's K terms is taken by the next reverse step, the only
+// one to need it.
 tdgl_status adjoint_step(tdgl_ctx *c, const AdjLayout &L, int iprev, int inext, double ew, float *grad, int k) {
     float2 *newest = (k & 1) ? L.lamW2 : L.lamW, *older = (k & 1) ? L.lamW : L.lamW2;
-    const Inst &d = c->inst[0].d;
-    const long N = d.N;
+    const long N = c->inst[0].d.N;
     hipStream_t s = c->stream;
-    const int G = std::max(1, std::min(d.part_cap, 2048));
+    const int G = adj_groups(N);
     const float2 *psim = L.seg_psi + (size_t)iprev * N, *psin = L.seg_psi + (size_t)inext * N;
     const float *mum = L.seg_mu + (size_t)iprev * N;
-    const double *Km = L.seg_K + iprev, *Kn = L.seg_K + inext;
     // Poisson transpose: fbar = W G(W^-1 mubar)
-    hipLaunchKernelGGL(k_adj_prep_f, dim3(G), dim3(256), 0, s, c->d_inst, L.mubar);
-    enqueue_f_mean(c);
-    LAUNCHCHK();
-    tdgl_status e = enqueue_poisson(c, nullptr, false);
+    if (c->any_mg) {
+        hipLaunchKernelGGL(k_adj_prep_f, dim3(G), dim3(256), 0, s, c->d_inst, L.f);
+        enqueue_f_mean(c);
+        LAUNCHCHK();
+    }
+    tdgl_status e = enqueue_poisson(c, nullptr, false, L.f);
     if (e) return e;
-    // adjoint of the Poisson right side, links at K_n
-    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, c->d_inst, 1, Kn);
-    hipLaunchKernelGGL(k_adj_g, dim3(G), dim3(256), 0, s, c->d_inst, psin, L.t1);
-    launch_stencil<MODE_NS>(c, 0, psin, L.t2);
-    launch_stencil<MODE_NS>(c, 0, L.t1, L.t3);
-    hipLaunchKernelGGL(k_adj_facc, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, L.t2, L.t3);
-    hipLaunchKernelGGL(k_adj_edge_f, dim3(G), dim3(256), 0, s, c->d_inst, psin);
-    hipLaunchKernelGGL(k_adj_reduce, dim3(1), dim3(256), 0, s, c->d_inst, G, 0, ew, L.adj);
-    // J_av(psi_n, K_{n-1}) and the K update
-    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, c->d_inst, 1, Km);
-    hipLaunchKernelGGL(k_adj_jterm, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psin, L.adj);
-    hipLaunchKernelGGL(k_adj_reduce, dim3(1), dim3(256), 0, s, c->d_inst, G, 1, 0.0, L.adj);
+    // adjoint of the Poisson right side, links at K_n; J_av(psi_n, K_{n-1})
+    // and the K update
+    hipLaunchKernelGGL(k_adj_links, dim3(cdiv(c->inst[0].d.ny, 256)), dim3(256), 0, s, c->d_inst, L.seg_K + inext,
+                       L.seg_K + iprev, L.uxn);
+    const auto kf = c->any_yz ? k_adj_f<true> : k_adj_f<false>;
+    hipLaunchKernelGGL(kf, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psin, L.uxn, L.part);
+    hipLaunchKernelGGL(k_adj_jterm, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psin, L.part, k > 0 ? 1 : 0, k & 1,
+                       ew, L.adj);
     // the Crank-Nicolson system transposed
-    hipLaunchKernelGGL(k_adj_maxabs, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar);
-    hipLaunchKernelGGL(k_adj_reduce, dim3(1), dim3(256), 0, s, c->d_inst, G, 3, 0.0, L.adj);
-    hipLaunchKernelGGL(k_adj_assemble, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psim, mum, newest, older, k >= 2 ? 1 : 0, L.adj);
+    hipLaunchKernelGGL(k_adj_assemble, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psim, mum, newest, older,
+                       k >= 2 ? 1 : 0, L.part, L.adj);
     LAUNCHCHK();
     c->blk_a = 1;  // k_adj_assemble's warm start stands for iterate 1
     e = jacobi_loop(c, nullptr, nullptr, 0);
     if (e) return e;
     // sources: eps gradient, mubar^-, K terms and psibar^-
-    hipLaunchKernelGGL(k_adj_scale_nu, dim3(G), dim3(256), 0, s, c->d_inst, L.adj, older);
-    launch_stencil<MODE_NS>(c, 0, older, L.t2);
-    hipLaunchKernelGGL(k_adj_edge_s, dim3(G), dim3(256), 0, s, c->d_inst, psim, psin, L.adj);
-    hipLaunchKernelGGL(k_adj_reduce, dim3(1), dim3(256), 0, s, c->d_inst, G, 2, 0.0, L.adj);
-    hipLaunchKernelGGL(k_adj_sources, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, L.mubar, grad, psim, psin,
-                       mum, L.t2, L.adj);
+    const auto ks = c->any_yz ? k_adj_sources<true> : k_adj_sources<false>;
+    hipLaunchKernelGGL(ks, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, L.f, grad, psim, psin, mum, older, L.part,
+                       L.adj);
     LAUNCHCHK();
     return TDGL_OK;
 }
@@ -2771,20 +2767,20 @@ tdgl_status voltage_grad_check(tdgl_ctx *ctx, int nsteps, int window_begin, int 
 }
 
 // Forward with checkpoints, then the reverse sweep, on the adjoint buffers
-// carved from ws (adj_layout(N, nsteps, C) bytes, 256-byte aligned).
+// carved from ws (adj_layout(N, ny, nsteps, C) bytes, 256-byte aligned).
 tdgl_status voltage_grad_run(tdgl_ctx *ctx, int nsteps, int window_begin, int C, char *ws, double *vbar,
                              float *grad) {
     const InstHost &h = ctx->inst[0];
     const long N = h.d.N;
     AdjLayout L;
-    adj_layout(N, nsteps, C, ws, &L);
+    adj_layout(N, h.d.ny, nsteps, C, ws, &L);
     hipStream_t s = ctx->stream;
     const int G = std::max(1, std::min(h.d.part_cap, 2048));
     hipLaunchKernelGGL(k_fill_f, dim3(fill_grid(N)), dim3(256), 0, s, grad, N, 0.f);
     hipLaunchKernelGGL(k_fill_c, dim3(fill_grid(N)), dim3(256), 0, s, L.psibar, N, 0.f, 0.f);
     hipLaunchKernelGGL(k_fill_c, dim3(fill_grid(N)), dim3(256), 0, s, L.lamW, N, 0.f, 0.f);
     hipLaunchKernelGGL(k_fill_c, dim3(fill_grid(N)), dim3(256), 0, s, L.lamW2, N, 0.f, 0.f);
-    hipLaunchKernelGGL(k_fill_f, dim3(fill_grid(N)), dim3(256), 0, s, L.mubar, N, 0.f);
+    hipLaunchKernelGGL(k_fill_f, dim3(fill_grid(N)), dim3(256), 0, s, L.f, N, 0.f);
     hipLaunchKernelGGL(k_adj_zero, dim3(1), dim3(64), 0, s, L.adj);
     LAUNCHCHK();
     // forward with checkpoints; the states of the last segment go straight
@@ -2799,21 +2795,24 @@ tdgl_status voltage_grad_run(tdgl_ctx *ctx, int nsteps, int window_begin, int C,
         if (n % C == 0) {
             const int q = n / C;
             hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.ck_psi + (size_t)q * N,
-                               L.ck_mu + (size_t)q * N, L.ck_K + 3 * q, 1);
+                               L.ck_mu + (size_t)q * N, L.ck_K + 3 * q, 1, (double *)nullptr);
         }
         if (n == s0_last)
-            hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.seg_psi, L.seg_mu, L.seg_K, 0);
+            hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.seg_psi, L.seg_mu, L.seg_K, 0,
+                               (double *)nullptr);
         tdgl_status e = tdgl_step(ctx, 1, nullptr);
         if (e) return e;
         fw_sweeps[n] = ctx->last_sweeps;
-        hipLaunchKernelGGL(k_adj_logE, dim3(1), dim3(64), 0, s, ctx->d_inst, L.Elog, n);
         if (n >= s0_last) {
             const int j = n + 1 - s0_last;
             hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.seg_psi + (size_t)j * N,
-                               L.seg_mu + (size_t)j * N, L.seg_K + j, 0);
+                               L.seg_mu + (size_t)j * N, L.seg_K + j, 0, L.Elog + n);
+        } else {
+            hipLaunchKernelGGL(k_adj_logE, dim3(1), dim3(64), 0, s, ctx->d_inst, L.Elog, n);
         }
     }
-    hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.fin_psi, L.fin_mu, L.fin_K, 1);
+    hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.fin_psi, L.fin_mu, L.fin_K, 1,
+                       (double *)nullptr);
     HIPCHK(hipMemcpyAsync(L.fin_st, h.d.st, sizeof(DevState), hipMemcpyDeviceToDevice, s));
     LAUNCHCHK();
     // reverse sweep, segment by segment (the last one is already stored)
@@ -2823,9 +2822,9 @@ tdgl_status voltage_grad_run(tdgl_ctx *ctx, int nsteps, int window_begin, int C,
         if (q != ncp - 1) {
             hipLaunchKernelGGL(k_adj_load, dim3(G), dim3(256), 0, s, ctx->d_inst, L.ck_psi + (size_t)q * N,
                                L.ck_mu + (size_t)q * N, L.ck_K + 3 * q);
-            hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, ctx->d_inst, 1, (const double *)nullptr);
+            hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, ctx->d_inst, 1);
             hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.seg_psi, L.seg_mu, L.seg_K,
-                               0);
+                               0, (double *)nullptr);
             LAUNCHCHK();
             for (int j = 1; j <= s1 - s0; ++j) {
                 // a replayed step whose forward solve took sw sweeps runs
@@ -2837,7 +2836,7 @@ tdgl_status voltage_grad_run(tdgl_ctx *ctx, int nsteps, int window_begin, int C,
                                                                            : tdgl_step(ctx, 1, nullptr);
                 if (e) return e;
                 hipLaunchKernelGGL(k_adj_save, dim3(G), dim3(256), 0, s, ctx->d_inst, L.seg_psi + (size_t)j * N,
-                                   L.seg_mu + (size_t)j * N, L.seg_K + j, 0);
+                                   L.seg_mu + (size_t)j * N, L.seg_K + j, 0, (double *)nullptr);
             }
         }
         for (int n = s1; n > s0; --n) {
@@ -2849,7 +2848,7 @@ tdgl_status voltage_grad_run(tdgl_ctx *ctx, int nsteps, int window_begin, int C,
     // back to the state after the forward run
     HIPCHK(hipMemcpyAsync(h.d.st, L.fin_st, sizeof(DevState), hipMemcpyDeviceToDevice, s));
     hipLaunchKernelGGL(k_adj_load, dim3(G), dim3(256), 0, s, ctx->d_inst, L.fin_psi, L.fin_mu, L.fin_K);
-    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, ctx->d_inst, 1, (const double *)nullptr);
+    hipLaunchKernelGGL(k_links, dim3(1), dim3(256), 0, s, ctx->d_inst, 1);
     hipLaunchKernelGGL(k_adj_vbar, dim3(1), dim3(64), 0, s, L.Elog, window_begin, nsteps, L.vbar);
     LAUNCHCHK();
     HIPCHK(hipMemcpyAsync(vbar, L.vbar, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -2896,7 +2895,7 @@ extern "C" {
 tdgl_status tdgl_adjoint_plan(const tdgl_ctx *ctx, int nsteps, int ckpt_every, size_t *bytes) {
     if (!ctx || !bytes) return fail(TDGL_EINVAL, "null argument");
     if (nsteps < 1 || ckpt_every < 1) return fail(TDGL_EINVAL, "nsteps and ckpt_every must be >= 1");
-    *bytes = adj_layout(ctx->inst[0].d.N, nsteps, std::min(ckpt_every, nsteps), nullptr, nullptr);
+    *bytes = adj_layout(ctx->inst[0].d.N, ctx->inst[0].d.ny, nsteps, std::min(ckpt_every, nsteps), nullptr, nullptr);
     return TDGL_OK;
 }
 
@@ -2905,7 +2904,7 @@ tdgl_status tdgl_voltage_grad(tdgl_ctx *ctx, int nsteps, int window_begin, int c
     tdgl_status e = voltage_grad_check(ctx, nsteps, window_begin, ckpt_every, vbar, grad);
     if (e) return e;
     const int C = std::min(ckpt_every, nsteps);
-    const size_t need = adj_layout(ctx->inst[0].d.N, nsteps, C, nullptr, nullptr);
+    const size_t need = adj_layout(ctx->inst[0].d.N, ctx->inst[0].d.ny, nsteps, C, nullptr, nullptr);
     if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < need)
         return fail(TDGL_EWS, "adjoint workspace missing, misaligned or below %zu bytes", need);
     return voltage_grad_run(ctx, nsteps, window_begin, C, (char *)ws, vbar, grad);
@@ -2916,7 +2915,7 @@ tdgl_status tdgl_voltage_grad_noalloc(tdgl_ctx *ctx, int nsteps, int window_begi
     tdgl_status e = voltage_grad_check(ctx, nsteps, window_begin, ckpt_every, vbar, grad);
     if (e) return e;
     const int C = std::min(ckpt_every, nsteps);
-    const size_t need = adj_layout(ctx->inst[0].d.N, nsteps, C, nullptr, nullptr);
+    const size_t need = adj_layout(ctx->inst[0].d.N, ctx->inst[0].d.ny, nsteps, C, nullptr, nullptr);
     if (need > kScratchBytes)
         return fail(TDGL_EWS,
                     "tdgl_voltage_grad_noalloc: %d steps with a checkpoint every %d on %ld nodes need %zu bytes of "

@@ -5,23 +5,6 @@
 
 namespace tdgl {
 
-// exp(i phi) in double precision with the argument reduced to [-pi, pi]
-// first, rounded to complex64.
-__device__ __forceinline__ float2 expi(double phi) {
-    const double twopi = 6.283185307179586476925286766559;
-    phi -= twopi * rint(phi / twopi);
-    double s, c;
-    sincos(phi, &s, &c);
-    return make_float2((float)c, (float)s);
-}
-
-// y offset of the x links: ybar_j = j hy - y_ref with y_ref = Ly/2 for the
-// xz-plane field (Eq. A_xz) and 0 for the yz-plane field (see k_links).
-__device__ __forceinline__ double link_yref(const Inst &I, const DevState *st) {
-    const double Ly = I.per[1] ? I.ny * I.hy : (I.ny - 1) * I.hy;
-    return st->yz ? 0.0 : 0.5 * Ly;
-}
-
 // Link tables of one instance.  xz-plane field, Landau gauge (Eq. A_xz,
 // Eq. link_variables, Sec. 3.3.1):
 //   ux[j] = exp(+i hx (K + Bz ybar_j)),  uz[j] = exp(-i hz Bx ybar_j),
@@ -37,16 +20,12 @@ __device__ __forceinline__ double link_yref(const Inst &I, const DevState *st) {
 // (same flux through every plaquette and the same phase around every
 // periodic loop; z must be open when By != 0).
 // One work-group per instance (grid = ninst); `which` = 1 refreshes ux only.
-// Kp (the adjoint's replay): K = *Kp is stored in the state first and the
-// links are those at it.
-__global__ void k_links(const Inst *__restrict__ insts, int which, const double *Kp) {
+__global__ void k_links(const Inst *__restrict__ insts, int which) {
     const Inst &I = insts[blockIdx.x];
     DevState *st = I.st;
     const double Ly = I.per[1] ? I.ny * I.hy : (I.ny - 1) * I.hy;
     const double Lx = I.per[0] ? I.nx * I.hx : (I.nx - 1) * I.hx;
-    const double Kn = Kp ? *Kp : st->K;
-    if (Kp && threadIdx.x == 0) st->K = Kn;
-    const double K = I.driven ? Kn : 0.0, Bx = st->Bx, Bz = st->Bz, By = st->By;
+    const double K = I.driven ? st->K : 0.0, Bx = st->Bx, Bz = st->Bz, By = st->By;
     const bool yz = st->yz != 0;
     const double yref = link_yref(I, st);
     for (int j = threadIdx.x; j < I.ny; j += blockDim.x) {

@@ -13,10 +13,7 @@
 //               writing b/M_mm, (ht/2)/M_mm and psi^(1);
 //   MODE_SWEEP  one Jacobi iteration psi^(l+1) = b/M + (ht/2)/M * NS(psi^(l));
 //   MODE_RHS    right side of the Poisson equation (Sec. 3.2);
-//   MODE_ENERGY free-energy density summed in FP64;
-//   MODE_NS     the neighbour sum NS(x) of an arbitrary complex field x (the
-//               off-diagonal part of the covariant Laplacian; used by the
-//               adjoint).
+//   MODE_ENERGY free-energy density summed in FP64.
 // FIRST and SWEEP also reduce max_m |r_m|^2 of their input iterate
 // (Eq. convergence) through r = M_mm (psi^(l+1) - psi^(l)).
 #include "kernels.h"
@@ -38,7 +35,7 @@ namespace tdgl {
 // l - 1 it has read to the host, tagged seq.
 template <int MODE, int R, bool NT, bool YZ>
 __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, const int *__restrict__ prefix,
-                                             int ninst, int l, const float2 *ext_in, float2 *ext_out, int b,
+                                             int ninst, int l, int b,
                                              unsigned long long *pub, unsigned seq) {
     constexpr int ROWS = R;
     constexpr int TYv = 4 * R;
@@ -95,8 +92,7 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
 
     const int cur = st->cur;
     const gf2 *__restrict__ src =
-        (const gf2 *)((MODE == MODE_NS) ? ext_in : (MODE == MODE_SWEEP) ? I.psi[cur ^ (l & 1)] : I.psi[cur]);
-    gf2 *__restrict__ nsout = (gf2 *)ext_out;
+        (const gf2 *)((MODE == MODE_SWEEP) ? I.psi[cur ^ (l & 1)] : I.psi[cur]);
     gf2 *__restrict__ dst = (gf2 *)I.psi[cur ^ ((l + 1) & 1)];
     const gf2 *__restrict__ Pt = (const gf2 *)I.P;
     const gf2 *__restrict__ bhp = (const gf2 *)I.bh;
@@ -300,10 +296,6 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
                     ns = nsum_in(uxk[r], uz[r], xm, xp, ym, yp, pmk[r], pnk[r], cx, cy, cz);
                 else
                     ns = nsum(uxk[r], uz[r], xm, xp, ym, yp, pmk[r], pnk[r], zm, zp, cx, cy, cz);
-                if (MODE == MODE_NS) {
-                    if (vy[r]) st2(nsout + pbase, m, ns);
-                    continue;
-                }
                 if (MODE == MODE_RHS) {
                     // f = sum_a (1/h_a^2) Im[psi^* (U psi_+ + U^* psi_-)] = Im[psi^* NS]
                     const float fv = rhs_node(c, ns);
@@ -357,9 +349,7 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     }
     const float rmax = __uint_as_float(rmaxb);
 
-    if (MODE == MODE_NS) {
-        return;
-    } else if (is_first_mode(MODE) || MODE == MODE_SWEEP) {
+    if (is_first_mode(MODE) || MODE == MODE_SWEEP) {
         if (timing || fixp) return;
         __syncthreads();
         wg_max_to<WG>(row_slot(I.res, I.rstride, l, b), rmax, reinterpret_cast<float *>(red));
@@ -372,9 +362,9 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
 template <int MODE, int R, bool NT, bool YZ>
 __global__ __launch_bounds__(WG) void k_stencil(const Inst *__restrict__ insts,
                                                 const int *__restrict__ prefix, int ninst, int l,
-                                                const float2 *ext_in, float2 *ext_out, unsigned long long *pub,
+                                                unsigned long long *pub,
                                                 unsigned seq) {
-    stencil_tile<MODE, R, NT, YZ>(insts, prefix, ninst, l, ext_in, ext_out, xcd_remap(blockIdx.x, gridDim.x), pub,
+    stencil_tile<MODE, R, NT, YZ>(insts, prefix, ninst, l, xcd_remap(blockIdx.x, gridDim.x), pub,
                               seq);
 }
 
@@ -411,15 +401,15 @@ __global__ __launch_bounds__(WG) void k_jacobi_persist(const Inst *__restrict__ 
             if (!go) break;
         }
         for (int t = blockIdx.x; t < ntiles; t += gridDim.x)
-            stencil_tile<MODE_SWEEP, R, NT, false>(insts, prefix, ninst, timing ? -1 : l, nullptr, nullptr,
+            stencil_tile<MODE_SWEEP, R, NT, false>(insts, prefix, ninst, timing ? -1 : l,
                                             xcd_remap(t, ntiles), nullptr, 0u);
         grid.sync();
     }
 }
 
 #define TDGL_INST(M, R, NT, YZ)                                                                            \
-    template __global__ void k_stencil<M, R, NT, YZ>(const Inst *, const int *, int, int, const float2 *, float2 *, \
-                                                     unsigned long long *, unsigned);
+    template __global__ void k_stencil<M, R, NT, YZ>(const Inst *, const int *, int, int, unsigned long long *, \
+                                                     unsigned);
 // YZ: a yz-plane field in the context (per-plane x-link factor)
 #define TDGL_INST_R(R)                      \
     TDGL_INST(MODE_FIRST, R, false, false)  \
@@ -430,7 +420,6 @@ __global__ __launch_bounds__(WG) void k_jacobi_persist(const Inst *__restrict__ 
     TDGL_INST(MODE_SWEEP, R, true, false)   \
     TDGL_INST(MODE_RHS, R, false, false)    \
     TDGL_INST(MODE_ENERGY, R, false, false) \
-    TDGL_INST(MODE_NS, R, false, false)     \
     TDGL_INST(MODE_FIRST, R, false, true)   \
     TDGL_INST(MODE_FIRST, R, true, true)    \
     TDGL_INST(MODE_FIRSTN, R, false, true)  \
@@ -438,8 +427,7 @@ __global__ __launch_bounds__(WG) void k_jacobi_persist(const Inst *__restrict__ 
     TDGL_INST(MODE_SWEEP, R, false, true)   \
     TDGL_INST(MODE_SWEEP, R, true, true)    \
     TDGL_INST(MODE_RHS, R, false, true)     \
-    TDGL_INST(MODE_ENERGY, R, false, true)  \
-    TDGL_INST(MODE_NS, R, false, true)
+    TDGL_INST(MODE_ENERGY, R, false, true)
 TDGL_INST_R(1)
 TDGL_INST_R(2)
 TDGL_INST_R(4)

@@ -4,7 +4,7 @@
 
 namespace tdgl {
 
-enum { MODE_FIRST = 0, MODE_SWEEP = 1, MODE_RHS = 2, MODE_ENERGY = 3, MODE_NS = 4, MODE_FIRSTN = 5 };
+enum { MODE_FIRST = 0, MODE_SWEEP = 1, MODE_RHS = 2, MODE_ENERGY = 3, MODE_FIRSTN = 4 };
 // MODE_FIRSTN: MODE_FIRST with the Langevin term (a separate instantiation,
 // so that the noiseless assemble carries none of the generator's registers).
 constexpr bool is_first_mode(int m) { return m == MODE_FIRST || m == MODE_FIRSTN; }
@@ -29,8 +29,8 @@ __global__ void k_sweep2i(const Inst *insts, const int *prefix, int ninst, int l
 template <int R, bool NT>
 __global__ void k_jacobi_persist(const Inst *insts, const int *prefix, int ninst, int l0, int lcap, int ntiles);
 template <int MODE, int R, bool NT, bool YZ>
-__global__ void k_stencil(const Inst *insts, const int *prefix, int ninst, int l, const float2 *ext_in,
-                          float2 *ext_out, unsigned long long *pub, unsigned seq);
+__global__ void k_stencil(const Inst *insts, const int *prefix, int ninst, int l, unsigned long long *pub,
+                          unsigned seq);
 
 // Threads of k_blk: one per (x, y) column of the block with an S-node halo.
 __host__ __device__ constexpr int blk_threads(int bx, int by, int s) {
@@ -45,7 +45,7 @@ __global__ void k_blk(const Inst *insts, const int *prefix, int ninst, int l, in
     X(32, 8, 4, 2, 2)        \
     X(32, 16, 1, 4, 0)
 
-__global__ void k_links(const Inst *insts, int which, const double *Kp);
+__global__ void k_links(const Inst *insts, int which);
 __global__ void k_solve_finalize(const Inst *insts, int ninst, int count_step, int nl, int fused,
                                  unsigned long long *pub, unsigned seq);
 __global__ void k_acc_reset(const Inst *insts, int ninst);
@@ -114,24 +114,24 @@ constexpr int FFT_YZ_BATCH = 8192;    // points it transforms at a time
 constexpr int FFT_YZ_LDS = 18432;     // its LDS, complex elements (144 KB)
 constexpr int FFT_X_PTS = 1024;       // complex points per work-group of the x passes (target)
 
-__global__ void k_adj_save(const Inst *insts, float2 *dpsi, float *dmu, double *dK, int raw);
+constexpr int ADJ_GROUPS = 1024;  // most work-groups of the adjoint's flat passes (a multiple of 256)
+__global__ void k_adj_save(const Inst *insts, float2 *dpsi, float *dmu, double *dK, int raw, double *elog);
 __global__ void k_adj_load(const Inst *insts, const float2 *spsi, const float *smu, const double *sK);
 __global__ void k_adj_logE(const Inst *insts, double *Elog, int n);
 __global__ void k_adj_vbar(const double *Elog, int wb, int nsteps, double *vbar);
 __global__ void k_adj_zero(AdjState *adj);
-__global__ void k_adj_prep_f(const Inst *insts, const float *mubar);
-__global__ void k_adj_g(const Inst *insts, const float2 *psin, float2 *g);
-__global__ void k_adj_facc(const Inst *insts, float2 *psibar, const float2 *ns_psi, const float2 *ns_g);
-__global__ void k_adj_edge_f(const Inst *insts, const float2 *psin);
-__global__ void k_adj_jterm(const Inst *insts, float2 *psibar, const float2 *psin, const AdjState *adj);
-__global__ void k_adj_maxabs(const Inst *insts, const float2 *psibar);
+__global__ void k_adj_prep_f(const Inst *insts, const float *f);
+__global__ void k_adj_links(const Inst *insts, const double *Kn, const double *Km, float2 *uxn);
+template <bool YZ>
+__global__ void k_adj_f(const Inst *insts, float2 *psibar, const float2 *psin, const float2 *uxn, double *part);
+__global__ void k_adj_jterm(const Inst *insts, float2 *psibar, const float2 *psin, double *part, int have2, int kp,
+                            double ew, AdjState *adj);
 __global__ void k_adj_assemble(const Inst *insts, const float2 *psibar, const float2 *psim, const float *mum,
-                               const float2 *lamW, const float2 *lamW_old, int extrap, const AdjState *adj);
-__global__ void k_adj_scale_nu(const Inst *insts, const AdjState *adj, float2 *tmp);
-__global__ void k_adj_sources(const Inst *insts, float2 *psibar, float *mubar, float *epsbar, const float2 *psim,
-                              const float2 *psin, const float *mum, const float2 *ns_l, const AdjState *adj);
-__global__ void k_adj_edge_s(const Inst *insts, const float2 *psim, const float2 *psin, const AdjState *adj);
-__global__ void k_adj_reduce(const Inst *insts, int nparts, int which, double ew, AdjState *adj);
+                               const float2 *lamW, const float2 *lamW_old, int extrap, const double *part,
+                               AdjState *adj);
+template <bool YZ>
+__global__ void k_adj_sources(const Inst *insts, float2 *psibar, float *f, float *epsbar, const float2 *psim,
+                              const float2 *psin, const float *mum, float2 *lamW, double *part, const AdjState *adj);
 
 __global__ void k_incl_first(const Inst *insts, int inst, const double *centres, const double *diam,
                              int nc, unsigned *first);

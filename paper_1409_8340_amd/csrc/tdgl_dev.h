@@ -71,9 +71,8 @@ struct StateScalars {
 
 // Scalars of the adjoint sweep over one step (device resident).
 struct AdjState {
-    double Kbar;   // adjoint of K, accumulated backwards through the steps
-    double Jbar;   // adjoint of J_av of the current step
-    double scale;  // normalisation of the adjoint Crank-Nicolson system
+    double Kbar[2];  // adjoint of K, accumulated backwards through the steps (the last and this one)
+    double scale;    // normalisation of the adjoint Crank-Nicolson system
     double pad;
 };
 
@@ -421,6 +420,23 @@ __device__ __forceinline__ double wg_sum(double v, double *lds_scratch) {
     if (threadIdx.x == 0)
         for (int i = 0; i < NT / 64; ++i) s += lds_scratch[i];
     return s;
+}
+
+// exp(i phi) in double precision with the argument reduced to [-pi, pi]
+// first, rounded to complex64.
+__device__ __forceinline__ float2 expi(double phi) {
+    const double twopi = 6.283185307179586476925286766559;
+    phi -= twopi * rint(phi / twopi);
+    double s, c;
+    sincos(phi, &s, &c);
+    return make_float2((float)c, (float)s);
+}
+
+// y offset of the x links: ybar_j = j hy - y_ref with y_ref = Ly/2 for the
+// xz-plane field (Eq. A_xz) and 0 for the yz-plane field (see k_links).
+__device__ __forceinline__ double link_yref(const Inst &I, const DevState *st) {
+    const double Ly = I.per[1] ? I.ny * I.hy : (I.ny - 1) * I.hy;
+    return st->yz ? 0.0 : 0.5 * Ly;
 }
 
 }  // namespace tdgl
