@@ -373,10 +373,12 @@ struct tdgl_ctx {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     Inst *d_inst = nullptr;
-    // prefix tables of the batched launches; multigrid ones per level:
-    // "all" = instances that have level l, "mid" = instances for which level
-    // l is not the coarsest (kMaxLevels * (n+1) each)
-    int *d_pref_st = nullptr, *d_pref_flat = nullptr, *d_pref_mg = nullptr, *d_pref_mid = nullptr;
+    // prefix tables of the batched launches.  Multigrid: level-0 tiles of every
+    // such instance and of those with one level only (2 (n + 1)); per level,
+    // tiles and blocks of the instances whose tail starts below it
+    // (kMaxLevels (n + 1) each)
+    int *d_pref_st = nullptr, *d_pref_flat = nullptr, *d_pref_mg = nullptr, *d_pref_mid = nullptr,
+        *d_pref_mgb = nullptr;
     int *d_pref_b = nullptr;  // blocks of the two-sweep boundary kernel per instance
     int *d_pref_i = nullptr;  // ... and of the interior (super-tile) kernel
     int *d_pref_sr = nullptr;  // ... and of the seam-ring pre-pass (seam2 instances)
@@ -413,7 +415,8 @@ struct tdgl_ctx {
         return f;
     }
     std::vector<hipEvent_t> evc;
-    int tot_st = 0, tot_flat = 0, tot_mg[kMaxLevels] = {0}, tot_mid[kMaxLevels] = {0};
+    int tot_st = 0, tot_flat = 0, tot_mg[2] = {0}, tot_mid[kMaxLevels] = {0},
+        tot_mgb[kMaxLevels] = {0};
     int nlev_max = 0;
     // spectral Poisson path: prefix tables of its three kernels and LDS sizes
     int *d_pref_fx = nullptr, *d_pref_fy = nullptr, *d_pref_fz = nullptr;
@@ -527,7 +530,8 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
     Inst *d_inst = cv.take<Inst>(n);
     int *pref_st = cv.take<int>(n + 1);
     int *pref_flat = cv.take<int>(n + 1);
-    int *pref_mg = cv.take<int>((size_t)kMaxLevels * (n + 1));
+    int *pref_mg = cv.take<int>(2 * (size_t)(n + 1));
+    int *pref_mgb = cv.take<int>((size_t)kMaxLevels * (n + 1));
     int *pref_mid = cv.take<int>((size_t)kMaxLevels * (n + 1));
     int *pref_fx = cv.take<int>(n + 1);
     int *pref_fy = cv.take<int>(n + 1);
@@ -708,6 +712,7 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
         ctx->d_pref_st = pref_st;
         ctx->d_pref_flat = pref_flat;
         ctx->d_pref_mg = pref_mg;
+        ctx->d_pref_mgb = pref_mgb;
         ctx->d_pref_mid = pref_mid;
         ctx->d_pref_fx = pref_fx;
         ctx->d_pref_fy = pref_fy;
@@ -846,8 +851,8 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         }
     // prefix tables
     const int n = ctx->n;
-    std::vector<int> ps(n + 1, 0), pf(n + 1, 0), pm((size_t)kMaxLevels * (n + 1), 0),
-        pmid((size_t)kMaxLevels * (n + 1), 0), pfx(n + 1, 0), pfy(n + 1, 0), pfz(n + 1, 0);
+    std::vector<int> ps(n + 1, 0), pf(n + 1, 0), pm(2 * (size_t)(n + 1), 0),
+        pmid((size_t)kMaxLevels * (n + 1), 0), pmgb((size_t)kMaxLevels * (n + 1), 0), pfx(n + 1, 0), pfy(n + 1, 0), pfz(n + 1, 0);
     std::vector<int> nps(n), npf(n), npm(n);
     for (int i = 0; i < n; ++i) {
         InstHost &h = ctx->inst[i];
@@ -857,12 +862,16 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         npf[i] = h.flat_blocks;
         npm[i] = !h.p.driven ? 0 : (h.d.fft ? h.fx_blocks : h.mg_blocks[0]);
         const bool mg = h.p.driven && !h.d.fft;
+        for (int l = 0; l < 2; ++l) {
+            const size_t o = (size_t)l * (n + 1) + i;
+            pm[o + 1] = pm[o] + ((mg && (l == 0 || h.d.nlev == 1)) ? h.mg_blocks[0] : 0);
+        }
         for (int l = 0; l < kMaxLevels; ++l) {
             const size_t o = (size_t)l * (n + 1) + i;
-            const int b = (mg && l < h.d.nlev) ? h.mg_blocks[l] : 0;
-            const int bm = (mg && l < h.d.mg_tail) ? h.mg_blocks[l] : 0;
-            pm[o + 1] = pm[o] + b;
-            pmid[o + 1] = pmid[o] + bm;
+            const bool above = mg && l < h.d.mg_tail;
+            const MGLevel &L = h.d.lev[l];
+            pmid[o + 1] = pmid[o] + (above ? h.mg_blocks[l] : 0);
+            pmgb[o + 1] = pmgb[o] + (above ? cdiv(L.nx, MGB_X) * cdiv(L.ny, MGB_Y) * cdiv(L.nz, MGB_Z) : 0);
         }
         pfx[i + 1] = pfx[i] + h.fx_blocks;
         pfy[i + 1] = pfy[i] + h.fy_blocks;
@@ -900,10 +909,12 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
     }
     ctx->tot_st = ps[n];
     ctx->tot_flat = pf[n];
+    for (int l = 0; l < 2; ++l) ctx->tot_mg[l] = pm[(size_t)l * (n + 1) + n];
     for (int l = 0; l < kMaxLevels; ++l) {
-        ctx->tot_mg[l] = pm[(size_t)l * (n + 1) + n];
         ctx->tot_mid[l] = pmid[(size_t)l * (n + 1) + n];
+        ctx->tot_mgb[l] = pmgb[(size_t)l * (n + 1) + n];
     }
+    HIPCHK(hipMemcpy(ctx->d_pref_mgb, pmgb.data(), pmgb.size() * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_mid, pmid.data(), pmid.size() * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_fx, pfx.data(), (n + 1) * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_fy, pfy.data(), (n + 1) * 4, hipMemcpyHostToDevice));
@@ -940,6 +951,7 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
 }
 
 const int *pref_mg(tdgl_ctx *c, int l) { return c->d_pref_mg + (size_t)l * (c->n + 1); }
+const int *pref_mgb(tdgl_ctx *c, int l) { return c->d_pref_mgb + (size_t)l * (c->n + 1); }
 const int *pref_mid(tdgl_ctx *c, int l) { return c->d_pref_mid + (size_t)l * (c->n + 1); }
 
 // Resolve the recorded event pairs into the per-class sums (waits for the
@@ -1153,23 +1165,23 @@ void launch_assemble(tdgl_ctx *c, int l = 0) {
 tdgl_status enqueue_vcycle(tdgl_ctx *c, int cyc) {
     hipStream_t s = c->stream;
     const int n = c->n;
-    auto grid = [](int b) { return dim3(std::max(b, 1)); };
-    {
+    auto blk = [&](auto fn, int h, int l, int isrc) {
+        hipLaunchKernelGGL(fn, dim3(c->tot_mgb[l]), dim3(mgb_threads(h)), 0, s, c->d_inst, pref_mgb(c, l), n, l, isrc,
+                           cyc, kOmega);
+    };
+    // the cycle before leaves the finest residual, but for the first and for
+    // hierarchies of one level
+    const int who = cyc == 0 ? 0 : 1;
+    if (c->tot_mg[who] > 0) {
         ProfScope ps(c, TDGL_K_MG_FINE);
-        hipLaunchKernelGGL(k_mg_residual, grid(c->tot_mg[0]), dim3(256), 0, s, c->d_inst, pref_mg(c, 0), n, 0,
-                           0, cyc);
+        hipLaunchKernelGGL(k_mg_residual, dim3(c->tot_mg[who]), dim3(256), 0, s, c->d_inst, pref_mg(c, who), n, cyc);
     }
     for (int l = 0; l < c->mg_tail; ++l) {
         ProfScope ps(c, TDGL_K_MG_COARSE);
-        if (l >= 1) {
-            hipLaunchKernelGGL(k_mg_smooth, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l), n,
-                               l, 0, 1, cyc, kOmega);
-            hipLaunchKernelGGL(k_mg_residual, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l),
-                               n, l, 1, cyc);
-        }
+        if (l >= 1) blk(k_mg_blk<false, 1, true>, 2, l, 0);
         // restrict into level l+1 for the instances whose tail starts below it
         if (c->tot_mid[l + 1] > 0)
-            hipLaunchKernelGGL(k_mg_restrict, grid(c->tot_mid[l + 1]), dim3(256), 0, s, c->d_inst,
+            hipLaunchKernelGGL(k_mg_restrict, dim3(c->tot_mid[l + 1]), dim3(256), 0, s, c->d_inst,
                                pref_mid(c, l + 1), n, l, cyc, kOmega);
     }
     {
@@ -1182,15 +1194,13 @@ tdgl_status enqueue_vcycle(tdgl_ctx *c, int cyc) {
     }
     for (int l = c->mg_tail - 1; l >= 0; --l) {
         ProfScope ps(c, l == 0 ? TDGL_K_MG_FINE : TDGL_K_MG_COARSE);
-        const int ifine = (l == 0) ? 0 : 1;
-        hipLaunchKernelGGL(k_mg_prolong, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l), n, l,
-                           ifine, cyc);
-        const int nsm = (l == 0) ? 4 : 2;
-        for (int it = 0; it < nsm; ++it) {
-            const int a = (l == 0) ? (it & 1) : ((it & 1) ^ 1);
-            hipLaunchKernelGGL(k_mg_smooth, grid(c->tot_mid[l]), dim3(256), 0, s, c->d_inst, pref_mid(c, l), n,
-                               l, a, a ^ 1, cyc, kOmega);
+        if (l > 0) {
+            blk(k_mg_blk<true, 2, false>, 2, l, 1);
+            continue;
         }
+        hipLaunchKernelGGL(k_mg_prolong, dim3(c->tot_mid[0]), dim3(256), 0, s, c->d_inst, pref_mid(c, 0), n, cyc);
+        blk(k_mg_blk<false, 2, false>, 2, 0, 0);
+        blk(k_mg_blk<false, 2, true>, 3, 0, 1);
     }
     LAUNCHCHK();
     return TDGL_OK;

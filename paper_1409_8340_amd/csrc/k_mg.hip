@@ -16,8 +16,8 @@
 // so any node count coarsens, at the price of a non-uniform coarse spacing.
 // Transfers are linear interpolation and its volume-weighted transpose.
 //
-// Kernels map one thread to one (x, y) column of a 64 x 4 tile and march
-// through a chunk of z planes, keeping the z neighbours in registers.
+// The restriction, the first residual and the mean map one thread to one
+// (x, y) column of a 64 x 4 tile and march through a chunk of z planes.
 #include "kernels.h"
 #include "stencil.h"
 
@@ -83,69 +83,23 @@ __device__ __forceinline__ ColCoef col_coef(const MGLevel &L, int x, int y) {
     return c;
 }
 
-// Damped Jacobi sweep dst = src + omega (rhs - A src) / D on level lv.
-// Level 0 subtracts the weighted mean of f from its right side (projection
-// onto the range of the singular operator).
-__global__ __launch_bounds__(256) void k_mg_smooth(const Inst *__restrict__ insts,
-                                                   const int *__restrict__ prefix, int ninst,
-                                                   int lv, int isrc, int idst, int cyc,
-                                                   float omega) {
-    const int ii = find_inst(prefix, ninst, blockIdx.x);
-    const Inst &I = insts[ii];
-    if (mg_done(I, cyc)) return;
-    const MGLevel &L = I.lev[lv];
-    const MGCols q = mg_map(L, blockIdx.x - prefix[ii]);
-    if (!q.valid) return;
-    const float *__restrict__ src = L.mu[isrc];
-    float *__restrict__ dst = L.mu[idst];
-    const float fm = (lv == 0) ? (float)I.st->f_mean : 0.f;
-    const ColCoef c = col_coef(L, q.x, q.y);
-    const long nxy = (long)L.nx * L.ny;
-    const long col = (long)q.y * L.nx + q.x;
-    const int zper = L.per[2];
-    const int km = wrapi(q.k0 - 1, L.nz, zper);
-    float mprev = src[km * nxy + col];
-    float mc = src[q.k0 * nxy + col];
-    for (int k = q.k0; k < q.k1; ++k) {
-        const int kp = wrapi(k + 1, L.nz, zper);
-        const float mnext = src[kp * nxy + col];
-        const long pb = k * nxy;
-        const float apz = L.ap[2][k], amz = L.am[2][k];
-        const float Amu = c.apx * (src[pb + q.y * (long)L.nx + c.xp] - mc) +
-                          c.amx * (src[pb + q.y * (long)L.nx + c.xm] - mc) +
-                          c.apy * (src[pb + c.yp * (long)L.nx + q.x] - mc) +
-                          c.amy * (src[pb + c.ym * (long)L.nx + q.x] - mc) +
-                          apz * (mnext - mc) + amz * (mprev - mc);
-        const float D = -(c.apx + c.amx + c.apy + c.amy + apz + amz);
-        const float rhs = L.rhs[pb + col] - fm;
-        dst[pb + col] = (D != 0.f) ? mc + omega * (rhs - Amu) / D : mc;
-        mprev = mc;
-        mc = mnext;
-    }
-}
-
-// Residual r = rhs - A mu evaluated in double precision from the stored
-// single-precision iterate.  On level 0 it also reduces max |r| into the
-// cycle's convergence word and, when the previous cycle had already
-// converged, does nothing.
+// Residual r = rhs - A mu of the finest level before cycle cyc (the first, or
+// any of a hierarchy of one level; k_mg_blk makes the others), evaluated in
+// double precision from the stored single-precision iterate, and its max |r|
+// into the cycle's convergence row.  Nothing when the previous cycle had
+// already converged.
 __global__ __launch_bounds__(256) void k_mg_residual(const Inst *__restrict__ insts,
-                                                     const int *__restrict__ prefix, int ninst,
-                                                     int lv, int isrc, int cyc) {
+                                                     const int *__restrict__ prefix, int ninst, int cyc) {
     __shared__ float red[4];
     const int ii = find_inst(prefix, ninst, blockIdx.x);
     const Inst &I = insts[ii];
-    if (I.fft) return;  // spectral instances (level 0 is launched over all driven ones)
-    if (lv == 0) {
-        if (cyc > 0 && mg_done(I, cyc - 1)) return;
-    } else if (mg_done(I, cyc)) {
-        return;
-    }
-    const MGLevel &L = I.lev[lv];
+    if (cyc > 0 && mg_done(I, cyc - 1)) return;
+    const MGLevel &L = I.lev[0];
     const MGCols q = mg_map(L, blockIdx.x - prefix[ii]);
     float rmax = 0.f;
     if (q.valid) {
-        const float *__restrict__ src = L.mu[isrc];
-        const double fm = (lv == 0) ? I.st->f_mean : 0.0;
+        const float *__restrict__ src = L.mu[0];
+        const double fm = I.st->f_mean;
         const ColCoef c = col_coef(L, q.x, q.y);
         const long nxy = (long)L.nx * L.ny;
         const long col = (long)q.y * L.nx + q.x;
@@ -169,7 +123,7 @@ __global__ __launch_bounds__(256) void k_mg_residual(const Inst *__restrict__ in
             mc = mnext;
         }
     }
-    if (lv == 0) wg_max_to<256>(row_slot(I.mures, I.rstride, cyc, blockIdx.x), rmax, red);
+    wg_max_to<256>(row_slot(I.mures, I.rstride, cyc, blockIdx.x), rmax, red);
 }
 
 // Restriction of the residual of level lv to the right side of level lv+1
@@ -219,25 +173,24 @@ __global__ __launch_bounds__(256) void k_mg_restrict(const Inst *__restrict__ in
     }
 }
 
-// Coarse-to-fine correction mu_f += P e_c (linear interpolation per axis).
+// Coarse-to-fine correction mu += P e_c of the finest level (linear
+// interpolation per axis).
 __global__ __launch_bounds__(256) void k_mg_prolong(const Inst *__restrict__ insts,
                                                     const int *__restrict__ prefix, int ninst,
-                                                    int lv, int ifine, int cyc) {
+                                                    int cyc) {
     const int ii = find_inst(prefix, ninst, blockIdx.x);
     const Inst &I = insts[ii];
     if (mg_done(I, cyc)) return;
-    // the coarsest level keeps its result in buffer 0, other levels in 1
-    const int icoarse = (lv + 1 == I.nlev - 1) ? 0 : 1;
-    const MGLevel &F = I.lev[lv];
-    const MGLevel &C = I.lev[lv + 1];
+    const MGLevel &F = I.lev[0];
+    const MGLevel &C = I.lev[1];
     const MGCols q = mg_map(F, blockIdx.x - prefix[ii]);
     if (!q.valid) return;
     const int kx0 = F.pk[0][2 * q.x], kx1 = F.pk[0][2 * q.x + 1];
     const float wx0 = F.pw[0][2 * q.x], wx1 = F.pw[0][2 * q.x + 1];
     const int ky0 = F.pk[1][2 * q.y], ky1 = F.pk[1][2 * q.y + 1];
     const float wy0 = F.pw[1][2 * q.y], wy1 = F.pw[1][2 * q.y + 1];
-    const float *__restrict__ ec = C.mu[icoarse];
-    float *__restrict__ mf = F.mu[ifine];
+    const float *__restrict__ ec = C.mu[0];
+    float *__restrict__ mf = F.mu[0];
     const long cnxy = (long)C.nx * C.ny, fnxy = (long)F.nx * F.ny;
     for (int k = q.k0; k < q.k1; ++k) {
         const int kz0 = F.pk[2][2 * k], kz1 = F.pk[2][2 * k + 1];
@@ -251,6 +204,158 @@ __global__ __launch_bounds__(256) void k_mg_prolong(const Inst *__restrict__ ins
         mf[k * fnxy + (long)q.y * F.nx + q.x] += e;
     }
 }
+
+// Smoothing passes of level lv on MGB_X x MGB_Y x MGB_Z blocks, from mu[isrc]
+// into the other buffer: the correction of the next coarser level first (PRO,
+// mu += P e_c by linear interpolation per axis), then S damped Jacobi sweeps
+//   mu <- mu + omega (rhs - A mu) / D,
+// then the residual r = rhs - A mu in double precision from the
+// single-precision iterate (RES; on level 0 with its max |r| into the next
+// cycle's convergence row).  Level 0 subtracts the weighted mean of f from its
+// right side (projection onto the range of the singular operator).
+// A pass over a coarse level is a chain of memory latencies of 5 us and more,
+// whatever its size, and each level above the tail had five of them, the
+// finest six.  A thread holds one (x, y) column of the block with a halo of one
+// node per sweep (and one for the residual), its planes in registers, the
+// block's planes in LDS; what a sweep gets wrong at the halo's rim moves in by
+// one node per sweep and never reaches the block.  Every load is issued before
+// the convergence rows are looked at, which only the stores wait for.  The
+// operations on a node and their order are those of one sweep, correction or
+// residual at a time, so are the bits.
+// Below 192 x 101 x 33: correction and two sweeps of 96 x 51 x 17 and 48 x 26 x
+// 9 nodes 10 us each (15 as three launches), a sweep and the residual 6.5 (10);
+// of the finest level two sweeps 11 us (16), two and the residual 19 (25).  The
+// finest level's correction stays a pass of its own (6 us): with the halo's
+// interpolation in front, its two sweeps took 27 us.  A run 9.9 -> 9.5 ms.
+template <bool PRO, int S, bool RES>
+__global__ __launch_bounds__(mgb_threads(S + RES)) void k_mg_blk(const Inst *__restrict__ insts,
+                                                                 const int *__restrict__ prefix, int ninst, int lv,
+                                                                 int isrc, int cyc, float omega) {
+    constexpr int H = S + RES, W = MGB_X + 2 * H, HT = MGB_Y + 2 * H, NP = MGB_Z + 2 * H, NT = mgb_threads(H);
+    __shared__ float buf[2][NP][W * HT];
+    __shared__ float red[NT / 64];
+    const int ii = find_inst(prefix, ninst, blockIdx.x);
+    const Inst &I = insts[ii];
+    const MGLevel &L = I.lev[lv];
+    const int nx = L.nx, ny = L.ny, nz = L.nz, nxy = nx * ny;
+    int b = blockIdx.x - prefix[ii];
+    const int bx = (nx + MGB_X - 1) / MGB_X, by = (ny + MGB_Y - 1) / MGB_Y;
+    const int x0 = b % bx * MGB_X;
+    b /= bx;
+    const int y0 = b % by * MGB_Y, k0 = b / by * MGB_Z;
+    const int t = min((int)threadIdx.x, W * HT - 1);  // (the last threads repeat the last column)
+    const int tx = t % W, ty = t / W, gx = x0 - H + tx, gy = y0 - H + ty;
+    // the slot's node: an image on a periodic axis; slots outside an open one
+    // are not read (they hold some node of the grid)
+    auto image = [](int g, int n, int per) { return per ? ((g % n) + n) % n : min(max(g, 0), n - 1); };
+    const int x = image(gx, nx, L.per[0]), y = image(gy, ny, L.per[1]);
+    const bool in = (int)threadIdx.x < W * HT && tx >= H && tx < H + MGB_X && ty >= H && ty < H + MGB_Y && gx < nx && gy < ny;
+    // neighbour slots (the node itself beyond an open face, as wrapi() has it,
+    // and at the halo's rim)
+    const int sxm = (tx == 0 || (!L.per[0] && gx == 0)) ? t : t - 1;
+    const int sxp = (tx == W - 1 || (!L.per[0] && gx == nx - 1)) ? t : t + 1;
+    const int sym = (ty == 0 || (!L.per[1] && gy == 0)) ? t : t - W;
+    const int syp = (ty == HT - 1 || (!L.per[1] && gy == ny - 1)) ? t : t + W;
+    const float *__restrict__ src = L.mu[isrc];
+    float *__restrict__ dst = L.mu[isrc ^ 1];
+    const float *__restrict__ rhsp = L.rhs;
+    const float apx = L.ap[0][x], amx = L.am[0][x], apy = L.ap[1][y], amy = L.am[1][y];
+    const double fmd = lv == 0 ? I.st->f_mean : 0.0;
+    const float fm = (float)fmd;
+    const int col = y * nx + x;
+    float v[NP], rh[NP], apz[NP], amz[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        const int k = image(k0 - H + q, nz, L.per[2]);
+        v[q] = src[k * nxy + col];
+        rh[q] = rhsp[k * nxy + col];
+        apz[q] = scalar_f(L.ap[2][k]);
+        amz[q] = scalar_f(L.am[2][k]);
+    }
+    if (PRO) {
+        const MGLevel &C = I.lev[lv + 1];
+        const float *__restrict__ ec = C.mu[0];
+        const int cnx = C.nx, cnxy = C.nx * C.ny;
+        const int kx0 = L.pk[0][2 * x], kx1 = L.pk[0][2 * x + 1];
+        const float wx0 = L.pw[0][2 * x], wx1 = L.pw[0][2 * x + 1];
+        const int ky0 = L.pk[1][2 * y], ky1 = L.pk[1][2 * y + 1];
+        const float wy0 = L.pw[1][2 * y], wy1 = L.pw[1][2 * y + 1];
+        const int c00 = ky0 * cnx + kx0, c01 = ky0 * cnx + kx1, c10 = ky1 * cnx + kx0, c11 = ky1 * cnx + kx1;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int k = image(k0 - H + q, nz, L.per[2]);
+            const float wz0 = scalar_f(L.pw[2][2 * k]), wz1 = scalar_f(L.pw[2][2 * k + 1]);
+            const int b0 = __builtin_amdgcn_readfirstlane(L.pk[2][2 * k]) * cnxy;
+            const int b1 = __builtin_amdgcn_readfirstlane(L.pk[2][2 * k + 1]) * cnxy;
+            const float e = wz0 * (wy0 * (wx0 * ec[b0 + c00] + wx1 * ec[b0 + c01]) +
+                                   wy1 * (wx0 * ec[b0 + c10] + wx1 * ec[b0 + c11])) +
+                            wz1 * (wy0 * (wx0 * ec[b1 + c00] + wx1 * ec[b1 + c01]) +
+                                   wy1 * (wx0 * ec[b1 + c10] + wx1 * ec[b1 + c11]));
+            v[q] += e;
+        }
+    }
+    const bool done = mg_done(I, cyc);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) buf[0][q][t] = v[q];
+    // z neighbours of plane q: the plane itself beyond an open face
+    auto zlo = [&](int q) { return !L.per[2] && k0 - H + q == 0 ? v[q] : v[q - 1]; };
+    auto zhi = [&](int q) { return !L.per[2] && k0 - H + q == nz - 1 ? v[q] : v[q + 1]; };
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        __syncthreads();
+        float nv[NP];
+        // (planes that the block's own do not depend on any more are left out)
+#pragma unroll
+        for (int q = s + 1; q < NP - 1 - s; ++q) {
+            const float *P = buf[s & 1][q];
+            const float mc = v[q], mnext = zhi(q), mprev = zlo(q);
+            const float Amu = apx * (P[sxp] - mc) + amx * (P[sxm] - mc) + apy * (P[syp] - mc) + amy * (P[sym] - mc) +
+                              apz[q] * (mnext - mc) + amz[q] * (mprev - mc);
+            const float D = -(apx + amx + apy + amy + apz[q] + amz[q]);
+            const float rhs = rh[q] - fm;
+            nv[q] = (D != 0.f) ? mc + omega * (rhs - Amu) / D : mc;
+        }
+#pragma unroll
+        for (int q = s + 1; q < NP - 1 - s; ++q) {
+            v[q] = nv[q];
+            if (s + 1 < S || RES) buf[(s & 1) ^ 1][q][t] = nv[q];
+        }
+    }
+    const int k1 = min(MGB_Z, nz - k0);
+    if (in && !done) {
+#pragma unroll
+        for (int q = 0; q < MGB_Z; ++q)
+            if (q < k1) dst[(k0 + q) * nxy + col] = v[H + q];
+    }
+    if (RES) {
+        float rmax = 0.f;
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < MGB_Z; ++c) {
+            const int q = H + c;
+            const float *P = buf[S & 1][q];
+            const double mc = v[q], mnext = zhi(q), mprev = zlo(q);
+            const double Amu = (double)apx * ((double)P[sxp] - mc) + (double)amx * ((double)P[sxm] - mc) +
+                               (double)apy * ((double)P[syp] - mc) + (double)amy * ((double)P[sym] - mc) +
+                               (double)apz[q] * (mnext - mc) + (double)amz[q] * (mprev - mc);
+            const double r = ((double)rh[q] - fmd) - Amu;
+            if (in && !done && c < k1) {
+                L.r[(k0 + c) * nxy + col] = (float)r;
+                const float ra = (float)fabs(r);
+                rmax = (ra > rmax || ra != ra) ? ra : rmax;
+            }
+        }
+        if (lv == 0 && !done && cyc + 1 < I.mu_max_cycles)
+            wg_max_to<NT>(row_slot(I.mures, I.rstride, cyc + 1, blockIdx.x), rmax, red);
+    }
+}
+#define TDGL_MG_INST(P, S, R) \
+    template __global__ void k_mg_blk<P, S, R>(const Inst *, const int *, int, int, int, int, float);
+TDGL_MG_INST(false, 1, true)
+TDGL_MG_INST(true, 2, false)
+TDGL_MG_INST(false, 2, false)
+TDGL_MG_INST(false, 2, true)
+#undef TDGL_MG_INST
 
 // Coarsest level L of a work-group: Jacobi sweeps in double precision on an
 // FP32 iterate until the residual falls below 1e-6 of the right side or 4000
@@ -589,7 +694,7 @@ __global__ __launch_bounds__(CO_THREADS) void k_mg_tail(const Inst *__restrict__
         e = m1;
     }
     const MGLevel &L = I.lev[lt];
-    for (int m = threadIdx.x; m < L.N; m += nt) L.mu[1][m] = e[m];
+    for (int m = threadIdx.x; m < L.N; m += nt) L.mu[0][m] = e[m];
 }
 template __global__ void k_mg_tail<1>(const Inst *, int, int, float);
 template __global__ void k_mg_tail<4>(const Inst *, int, int, float);

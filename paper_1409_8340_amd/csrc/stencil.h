@@ -243,11 +243,7 @@ __device__ __forceinline__ float2 nsum(float2 ux, float2 uz, float2 xm, float2 x
                        __builtin_fmaf(cx, xt.y, __builtin_fmaf(cy, yt.y, cz * zt.y)));
 }
 
-// A value that every lane of the wavefront holds, moved to scalar registers.
-__device__ __forceinline__ float2 to_scalar(float2 v) {
-    return make_float2(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.x))),
-                       __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.y))));
-}
+__device__ __forceinline__ float2 to_scalar(float2 v) { return make_float2(scalar_f(v.x), scalar_f(v.y)); }
 
 // nsum() at a node with both z neighbours (no branch): the same operations.
 __device__ __forceinline__ float2 nsum_in(float2 ux, float2 uz, float2 xm, float2 xp, float2 ym, float2 yp,

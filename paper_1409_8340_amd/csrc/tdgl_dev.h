@@ -439,4 +439,9 @@ __device__ __forceinline__ double link_yref(const Inst &I, const DevState *st) {
     return st->yz ? 0.0 : 0.5 * Ly;
 }
 
+// A value that every lane of the wavefront holds, in a scalar register.
+__device__ __forceinline__ float scalar_f(float v) {
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+
 }  // namespace tdgl
