@@ -424,6 +424,7 @@ struct tdgl_ctx {
     size_t fx_lds = 0, fy_lds = 0, fz_lds = 0;
     int fz_nzmax = 0;  // deepest z over the instances: scan rows per lane of the z solve
     bool fx_p2 = true, fy_p2 = true;  // every spectral instance has power-of-two nx (ny)
+    bool fft_psi = false;             // right sides of time steps made by the forward x transforms
     bool fft_yz = false;              // y transforms and z systems in one kernel (kx-major half spectrum)
     bool fx_long = false;             // some spectral instance has nx > FFT_X_PTS
     bool noisy = false;               // some instance has a Langevin term
@@ -550,9 +551,12 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
     unsigned *mures = cv.take<unsigned>((size_t)max_cycles * NSLOT * npad);
     // the fused y and z pass of the spectral solve, when every spectral
     // instance fits it
-    bool yz = true;
+    bool yz = true, even = true;
     for (int i = 0; i < n; ++i)
-        if (fft_eligible(params[i])) yz = yz && fft_yz_planes(params[i].nx, params[i].ny, params[i].nz) > 0;
+        if (fft_eligible(params[i])) {
+            yz = yz && fft_yz_planes(params[i].nx, params[i].ny, params[i].nz) > 0;
+            even = even && params[i].ny % 2 == 0;
+        }
     for (int i = 0; i < n; ++i) {
         const tdgl_params &p = params[i];
         InstHost &h = ih[i];
@@ -693,11 +697,13 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 {
                     // fft_x_pairs row pairs of a plane per group; up to eight
                     // groups per work-group while at least 2048 remain
-                    const long groups = (long)cdiv(p.ny, 2L * fft_x_pairs(p.nx, p.ny)) * p.nz;
+                    const long groups = (long)cdiv(fft_x_rows(p.ny, p.nz), 2L * fft_x_pairs(p.nx, p.ny)) *
+                                        fft_x_planes(p.ny, p.nz);
                     d.fxg = (int)std::max(1L, std::min(8L, groups / 2048));
                     h.fx_blocks = cdiv(groups, d.fxg);
                 }
                 d.fyz = yz ? fft_yz_planes(p.nx, p.ny, p.nz) : 0;
+                d.fpsi = yz && even;
                 h.fy_blocks = d.fyz ? cdiv(P, d.fyz) : fft_y_plan(p.nx, p.ny, p.nz).blocks;
                 h.fz_blocks = p.nz <= FFT_ZSERIAL ? cdiv(p.ny * P, 256) : p.ny * cdiv(P, FFT_ZTK);
             }
@@ -881,6 +887,7 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         if (h.d.fft) {
             ctx->any_fft = true;
             ctx->fft_yz = h.d.fyz > 0;
+            ctx->fft_psi = h.d.fpsi != 0;
             ctx->fx_lds = std::max(ctx->fx_lds, (size_t)fft_x_lds(h.p.nx, h.p.ny) * 8);
             ctx->fy_lds = std::max(ctx->fy_lds, h.d.fyz ? (size_t)fft_yz_lds(h.p.ny, h.p.nz, h.d.fyz) * 8
                                                         : ((size_t)fft_y_plan(h.p.nx, h.p.ny, h.p.nz).TK *
@@ -1461,7 +1468,7 @@ tdgl_status enqueue_fft(tdgl_ctx *ctx, bool step, const float *f = nullptr) {
     const int *pref = ctx->d_pref_fx;
     int nn = n;
     const float *in = f;
-    const int src = !step || !ctx->fft_yz ? SRC_F : (ctx->any_yz ? SRC_PSI_YZ : SRC_PSI);
+    const int src = !step || !ctx->fft_psi ? SRC_F : (ctx->any_yz ? SRC_PSI_YZ : SRC_PSI);
     {
         void *args[] = {(void *)&ins, (void *)&pref, (void *)&nn, (void *)&in};
         (void)hipLaunchKernel(fft_fwd_fn(ctx, src), gx, bx, args, ctx->fx_lds, s);
@@ -1521,9 +1528,10 @@ void enqueue_f_mean(tdgl_ctx *ctx) {
 // spectrum is too large for the fused y and z pass.  There the forward x
 // transform could make it from psi as well, but its work-groups then hold 136
 // registers and 875 us pass at 1024 x 1024 x 128 against 413 + 272 us for the
-// two passes; on 300 x 180 x 50 it takes 26 us against 15 + 15.
+// two passes; on 300 x 180 x 50 it takes 26 us against 15 + 15.  Nor does it
+// for odd ny, whose row pairs run on across planes.
 void enqueue_rhs(tdgl_ctx *ctx) {
-    if (!ctx->any_mg && ctx->fft_yz) return;
+    if (!ctx->any_mg && ctx->fft_psi) return;
     launch_rhs(ctx);
     if (ctx->any_mg)
         hipLaunchKernelGGL(k_reduce_to_state, dim3(ctx->n), dim3(256), 0, ctx->stream, ctx->d_inst, rhs_parts(ctx), 0, 2);
@@ -2581,7 +2589,7 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
         // the Poisson right side, where a pass of its own makes it, on the
         // chosen tile or on 64 x 16 tiles with four rows per thread,
         // whichever runs faster
-        if ((ctx->any_mg || (ctx->any_fft && !ctx->fft_yz)) && best.rows != 4) {
+        if ((ctx->any_mg || (ctx->any_fft && !ctx->fft_psi)) && best.rows != 4) {
             float rms[2];
             for (int q4 = 0; q4 < 2; ++q4) {
                 Tiling t = best;

@@ -246,6 +246,14 @@ __device__ __forceinline__ unsigned spec_at(int k, int y, int z, int ny, int nz,
               : ((unsigned)z * (unsigned)ny + (unsigned)y) * (unsigned)sp + (unsigned)k;
 }
 
+// Rows per plane and planes of the x passes.  The two rows of a complex
+// sequence are neighbours in memory, 2 j and 2 j + 1 of all ny nz rows, and
+// their partner enters both rows' rounding; where ny is odd the pairs run on
+// across planes, so there the whole grid counts as one plane (rows, values and
+// both forms of the spectrum are contiguous over y and z).
+__host__ __device__ int fft_x_rows(int ny, int nz) { return (ny & 1) ? ny * nz : ny; }
+__host__ __device__ int fft_x_planes(int ny, int nz) { return (ny & 1) ? 1 : nz; }
+
 // Groups of the x passes: rows y0 .. y0 + 2 pairs - 1 of plane k, in the order
 // of memory; a work-group takes I.fxg consecutive ones.
 struct XGroup {
@@ -296,8 +304,10 @@ __global__ __launch_bounds__(FFT_X_THREADS) void k_fft_fwd(const Inst *__restric
     const int lbg = TR ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int ii = find_inst(prefix, ninst, lbg);
     const Inst &I = insts[ii];
-    const int nx = I.nx, ny = I.ny, nz = I.nz, P = nx / 2 + 1, sp = I.sp;
-    const int pairs = fft_x_pairs(nx, ny);
+    // (the right side from psi is made for even ny only)
+    const int nx = I.nx, P = nx / 2 + 1, sp = I.sp;
+    const int ny = SRC == SRC_F ? fft_x_rows(I.ny, I.nz) : I.ny, nz = SRC == SRC_F ? fft_x_planes(I.ny, I.nz) : I.nz;
+    const int pairs = fft_x_pairs(nx, I.ny);
     const int ss = nx + 1;
     const int gy = (ny + 2 * pairs - 1) / (2 * pairs), ngr = gy * nz;
     const int g0 = (lbg - prefix[ii]) * I.fxg, g1 = min(g0 + I.fxg, ngr);
@@ -443,8 +453,10 @@ __global__ __launch_bounds__(FFT_X_THREADS) void k_fft_inv(const Inst *__restric
     const int lbg = TR ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int ii = find_inst(prefix, ninst, lbg);
     const Inst &I = insts[ii];
-    const int nx = I.nx, ny = I.ny, nz = I.nz, P = nx / 2 + 1, sp = I.sp;
-    const int pairs = fft_x_pairs(nx, ny);
+    const int nx = I.nx, P = nx / 2 + 1, sp = I.sp;
+    const int ny = fft_x_rows(I.ny, I.nz), nz = fft_x_planes(I.ny, I.nz);
+    const bool flat = ny != I.ny;  // rows of several planes in a group
+    const int pairs = fft_x_pairs(nx, I.ny);
     const int ss = nx + 1, R = 2 * pairs;
     const int gy = (ny + R - 1) / R, ngr = gy * nz;
     const int g0 = (lbg - prefix[ii]) * I.fxg, g1 = min(g0 + I.fxg, ngr);
@@ -527,14 +539,14 @@ __global__ __launch_bounds__(FFT_X_THREADS) void k_fft_inv(const Inst *__restric
             const unsigned m = (unsigned)k * NXY + (unsigned)(ya * nx + e);
             if (ya < ny) {
                 out[m] = w.x;
-                sum += (double)w.x;
+                sum += flat ? (double)volz[ya / I.ny] * (double)w.x : (double)w.x;
             }
             if (ya + 1 < ny) {
                 out[m + nx] = w.y;
-                sum += (double)w.y;
+                sum += flat ? (double)volz[(ya + 1) / I.ny] * (double)w.y : (double)w.y;
             }
         }
-        acc += (double)volz[k] * sum;
+        acc += flat ? sum : (double)volz[k] * sum;
         __syncthreads();
     }
     // x and y are periodic: one control volume each

@@ -68,8 +68,8 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
         if (pub && b == prefix[ii] && threadIdx.x == 0) publish(pub + (size_t)(l - 1) * ninst + ii, seq, prev);
         if (prev < I.tol) return;
     }
-    // with the fused y and z pass the spectral solve makes its own right side
-    if ((MODE == MODE_RHS) && (!I.driven || (I.fft && I.fyz > 0))) return;
+    // the spectral solve may make its own right side
+    if ((MODE == MODE_RHS) && (!I.driven || (I.fft && I.fpsi))) return;
 
     // the Poisson right side with four rows per thread has a 64 x 16 tiling
     // of its own (the same as the stencil's when the context's rows are 4)

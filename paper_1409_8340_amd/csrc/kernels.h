@@ -93,6 +93,8 @@ template <int RMAX>
 __global__ void k_fft_zsolve(const Inst *insts, const int *prefix, int ninst);
 __global__ void k_fft_tables(const Inst *insts, int inst);
 __host__ __device__ int fft_x_pairs(int nx, int ny);
+__host__ __device__ int fft_x_rows(int ny, int nz);
+__host__ __device__ int fft_x_planes(int ny, int nz);
 __host__ __device__ int fft_x_lds(int nx, int ny);
 __host__ __device__ int fft_yz_planes(int nx, int ny, int nz);
 __host__ __device__ int fft_yz_lds(int ny, int nz, int g);

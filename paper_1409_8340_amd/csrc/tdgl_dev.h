@@ -176,6 +176,7 @@ struct Inst {
     float2 *spec;        // half spectrum, nz * ny rows of pitch sp >= nx/2 + 1
     int sp;              // row pitch of spec (complex elements)
     int fxg;             // groups per work-group of the x passes (the next group's loads overlap the transform)
+    int fpsi;            // the forward x transform makes the right side of a time step from psi
     int fyz;             // kx planes per work-group of the fused y and z pass (0: separate passes)
     int fcpt;            // cells per thread of the flat reductions (J_av, |psi|^2)
     float2 *twx, *twy;   // twiddles exp(-2 pi i k / n) along x and y
