@@ -1452,7 +1452,7 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
 
 // Solve the Poisson equation of every driven instance: right side I.f,
 // solution into I.mu (level-0 mu[0]), then the weighted mean of mu.  Spectral
-// instances take the five FFT / z-solve passes; multigrid instances take
+// instances take the three or five FFT / z-solve passes; multigrid instances take
 // V-cycles until their stop rule, decided on the device and polled by the
 // host one cycle behind.  Statistics are accumulated into acc.
 // The passes of the spectral solve for every instance that uses it: three
@@ -2697,6 +2697,9 @@ struct AdjLayout {
     AdjState *adj;
 };
 
+// Work-groups of the adjoint's flat passes.
+int adj_groups(long N) { return std::max(1, std::min(cdiv(N, 256L), ADJ_GROUPS)); }
+
 size_t adj_layout(long N, int ny, int nsteps, int C, char *base, AdjLayout *L) {
     Carver cv{base};
     const int ncp = (nsteps + C - 1) / C;
@@ -2714,7 +2717,7 @@ size_t adj_layout(long N, int ny, int nsteps, int C, char *base, AdjLayout *L) {
     l.psibar = cv.take<float2>(N);
     l.f = cv.take<float>(N);
     l.uxn = cv.take<float2>(ny);
-    l.part = cv.take<double>(4 * ADJ_GROUPS);
+    l.part = cv.take<double>(4 * (size_t)adj_groups(N));
     l.lamW = cv.take<float2>(N);
     l.lamW2 = cv.take<float2>(N);
     l.Elog = cv.take<double>(nsteps);
@@ -2723,9 +2726,6 @@ size_t adj_layout(long N, int ny, int nsteps, int C, char *base, AdjLayout *L) {
     if (L) *L = l;
     return cv.off;
 }
-
-// Work-groups of the adjoint's flat passes.
-int adj_groups(long N) { return std::max(1, std::min(cdiv(N, 256L), ADJ_GROUPS)); }
 
 // Reverse of one step: prev = state n-1, nxt = state n (segment slots).
 // k: reverse steps done before this one.  The last two reverse steps'

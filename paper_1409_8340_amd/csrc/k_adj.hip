@@ -35,8 +35,6 @@
 
 namespace tdgl {
 
-constexpr int AG = ADJ_GROUPS;  // partials per sum
-
 __device__ __forceinline__ void node_ijk(const Inst &I, int m, int &i, int &j, int &k) {
     i = m % I.nx;
     const int r = m / I.nx;
@@ -178,12 +176,12 @@ __device__ __forceinline__ float2 adj_ns(const Inst &I, const AdjNb &b, int i, i
     return nsum(ux, I.uz[j], v[0], v[1], v[2], v[3], v[4], v[5], b.zm, b.zp, I.cx, I.cy, I.cz);
 }
 
-// Sums of NS arrays of n <= AG partials over a 256-thread work-group, in a
+// Sums of NS arrays of n <= ADJ_GROUPS partials over a 256-thread work-group, in a
 // fixed order, to all its threads.
 template <int NS>
 __device__ __forceinline__ void adj_sums(const double *const *part, int n, double *s) {
     __shared__ double red[NS][4];
-    constexpr int C = AG / 256;
+    constexpr int C = ADJ_GROUPS / 256;
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
         double v[C];
@@ -211,7 +209,7 @@ __device__ __forceinline__ void adj_sums(const double *const *part, int n, doubl
 //   psibar += -i fbar NS(psi) + i W NS(g);
 // partials of sum_m (fbar_m - fbar_{m+x}) Re[conj(psi_m) U_j psi_{m+x}] with U
 // at K_n (part[0..]) and, for J_av, of sum Re[conj(psi_m) U_j psi_{m+x}] with
-// U at K_{n-1} (part[AG..]).
+// U at K_{n-1} (part[G..], G work-groups in all four passes).
 template <bool YZ>
 __global__ __launch_bounds__(256) void k_adj_f(const Inst *__restrict__ insts, float2 *psibar, const float2 *psin,
                                                const float2 *uxn, double *part) {
@@ -249,22 +247,22 @@ __global__ __launch_bounds__(256) void k_adj_f(const Inst *__restrict__ insts, f
     const double s = wg_sum<256>(acc, red), sj = wg_sum<256>(accj, red);
     if (threadIdx.x == 0) {
         part[blockIdx.x] = s;
-        part[AG + blockIdx.x] = sj;
+        part[gridDim.x + blockIdx.x] = sj;
     }
 }
 
-// The K update's reverse from the partials (part[2 AG ..]: those of the
+// The K update's reverse from the partials (part[2 G ..]: those of the
 // reverse step before, have2),
 //   Kbar += (ht/2) S2 / hx;  Kbar += S0 / hx;  Jbar = -(dt Kbar + ew);
 //   Kbar += Jbar S1 / N   (from adj->Kbar[kp] to adj->Kbar[kp ^ 1]),
 // then psibar += -i Jbar (T psi) / (N hx) and partial maxima of |psibar| / w
-// (part[3 AG ..]).
+// (part[3 G ..]).
 __global__ __launch_bounds__(256) void k_adj_jterm(const Inst *__restrict__ insts, float2 *psibar,
                                                    const float2 *psin, double *part, int have2, int kp, double ew,
                                                    AdjState *adj) {
     __shared__ double red[4];
     const Inst &I = insts[0];
-    const double *src[3] = {part, part + AG, part + 2 * AG};
+    const double *src[3] = {part, part + gridDim.x, part + 2 * gridDim.x};
     double S[3];
     adj_sums<3>(src, (int)gridDim.x, S);
     double Kbar = adj->Kbar[kp];
@@ -289,7 +287,7 @@ __global__ __launch_bounds__(256) void k_adj_jterm(const Inst *__restrict__ inst
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
     __syncthreads();
-    if (threadIdx.x == 0) part[3 * AG + blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    if (threadIdx.x == 0) part[3 * gridDim.x + blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
 
 // Adjoint system of step n: M~ nu = W^-1 psibar / scale with M from
@@ -310,7 +308,7 @@ __global__ __launch_bounds__(256) void k_adj_assemble(const Inst *__restrict__ i
     __shared__ double mred[4];
     const Inst &I = insts[0];
     double mx = 0.0;
-    for (int t = threadIdx.x; t < (int)gridDim.x; t += 256) mx = fmax(mx, part[3 * AG + t]);
+    for (int t = threadIdx.x; t < (int)gridDim.x; t += 256) mx = fmax(mx, part[3 * gridDim.x + t]);
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
     if ((threadIdx.x & 63) == 0) mred[threadIdx.x >> 6] = mx;
     __syncthreads();
@@ -359,7 +357,7 @@ __global__ __launch_bounds__(256) void k_adj_assemble(const Inst *__restrict__ i
 
 // epsbar, f = W^-1 mubar^- (the next reverse step's Poisson right side) and
 // psibar^- from lambda = W scale nu; lambda / W into lamW (the next reverse
-// steps' warm start); partials (part[2 AG ..]) of
+// steps' warm start); partials (part[2 G ..]) of
 //   Re[i sum_m (conj(lambda_m) U_j s_{m+x} - conj(lambda_{m+x} U_j) s_m)],
 // s = psi^- + psi.
 template <bool YZ>
@@ -412,7 +410,7 @@ __global__ __launch_bounds__(256) void k_adj_sources(const Inst *__restrict__ in
         acc += -(double)(a.y - bb.y);
     }
     const double t = wg_sum<256>(acc, red);
-    if (threadIdx.x == 0) part[2 * AG + blockIdx.x] = t;
+    if (threadIdx.x == 0) part[2 * gridDim.x + blockIdx.x] = t;
 }
 
 template __global__ void k_adj_f<false>(const Inst *, float2 *, const float2 *, const float2 *, double *);
