@@ -68,8 +68,9 @@ __device__ __forceinline__ float2 nsum_sel(float2 ux, float2 uz, float2 xm, floa
 
 // One pass of ns <= S iterates from psi^(l) (FIRST: l = 0 and the assemble).
 // prefix: blocks per instance.  np: rows the previous pass wrote (l - np ..
-// l - 1); the pass exits when one of them met the tolerance, or when that
-// pass exited (rows never written read 0).  Pass number `pass` reads psi[cur ^
+// l - 1); the pass hands them to the host and exits when one of them met the
+// tolerance, when that pass exited (rows never written read 0) or when the
+// instance's cap is reached.  Pass number `pass` reads psi[cur ^
 // (pass & 1)] and writes the other buffer.  l = -1: timing (psi[cur] to the
 // spare buffer, nothing recorded); l = -2: the corrective pass of st->fix
 // iterates from psi[cur ^ 1] into psi[cur] (see k_solve_finalize).
@@ -100,7 +101,10 @@ __global__ __launch_bounds__(blk_threads(BX, BY, S)) void k_blk(const Inst *__re
         ns = st->fix;
         if (ns <= 0) return;
     } else if (!FIRST && !timing) {
-        if (l >= I.max_iter) return;
+        // an instance at its cap has no iterate left to make, but rows below
+        // the cap row that the host waits for while others iterate
+        const bool capped = l >= I.max_iter;
+        if (capped && !(pub && first_block)) return;
         // the two halves of a wavefront read two rows at a time
         bool done = false;
         for (int r = 0; r < np; r += 2) {
@@ -111,7 +115,7 @@ __global__ __launch_bounds__(blk_threads(BX, BY, S)) void k_blk(const Inst *__re
                 publish(pub + (size_t)row * ninst + ii, seq, v);
             done = done || __ballot(v < I.tol) != 0;
         }
-        if (done) return;
+        if (done || capped) return;
     }
     const int tx = (nx + BX - 1) / BX, ty = (ny + BY - 1) / BY;
     const int bx = q % tx;

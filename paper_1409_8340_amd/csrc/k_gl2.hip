@@ -153,7 +153,10 @@ __global__ __launch_bounds__(WG) void k_sweep2(const Inst *__restrict__ insts, c
         // that a skipped pass never wrote reads 0, so an earlier end shows
         // here too), and the buffer of psi^(l-1) must survive for the
         // corrective sweep
-        if (l >= I.max_iter) return;
+        // (at the instance's cap too, whose pair may have begun a row below
+        // the cap row: the host waits for that one while others iterate)
+        const bool capped = l >= I.max_iter;
+        if (capped && !(pub && q == 0)) return;
         const float p1 = row_max_wave(I.res, I.rstride, l - 1);
         const float p2 = (l >= 2) ? row_max_wave(I.res, I.rstride, l - 2) : 1.f;
         // hand rows l - 1 and l - 2 (written by the previous pass) to the host
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(WG) void k_sweep2(const Inst *__restrict__ insts, c
             publish(pub + (size_t)(l - 1) * ninst + ii, seq, p1);
             if (l >= 2) publish(pub + (size_t)(l - 2) * ninst + ii, seq, p2);
         }
-        if (p1 < I.tol) return;
+        if (capped || p1 < I.tol) return;
         if (l >= 2 && p2 < I.tol) return;
     }
     const bool rec2 = !timing && (l + 1 < I.max_iter);
@@ -495,16 +498,17 @@ __global__ __launch_bounds__(WG * sweep2i_mult(R, TY), 4) void k_sweep2i(const I
     const bool xper = I.per[0] != 0;
     const bool timing = l < 0;
     if (!timing) {
-        if (l >= I.max_iter) return;
+        const bool capped = l >= I.max_iter, hand = pub && I.nbt == 0 && first;
+        if (capped && !hand) return;
         const float p1 = row_max_wave(I.res, I.rstride, l - 1);
         const float p2 = (l >= 2) ? row_max_wave(I.res, I.rstride, l - 2) : 1.f;
         // an instance with no boundary tiles hands rows l - 1 and l - 2 to
         // the host from here (else the boundary kernel does)
-        if (pub && I.nbt == 0 && first && threadIdx.x == 0) {
+        if (hand && threadIdx.x == 0) {
             publish(pub + (size_t)(l - 1) * ninst + ii, seq, p1);
             if (l >= 2) publish(pub + (size_t)(l - 2) * ninst + ii, seq, p2);
         }
-        if (p1 < I.tol) return;
+        if (capped || p1 < I.tol) return;
         if (l >= 2 && p2 < I.tol) return;
     }
     if (!tile_interior2(x0, y0, TYv, nx, ny, xper, seam2)) return;
