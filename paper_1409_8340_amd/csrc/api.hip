@@ -433,7 +433,8 @@ struct tdgl_ctx {
     bool any_fft = false, any_mg = false;
     int co_nodes = 0;  // largest coarsest multigrid level
     int mg_tail = 0, tail_nodes = 0;  // largest first level of k_mg_tail, and its most nodes
-    size_t tail_lds = 0;              // its LDS
+    size_t tail_lds[2] = {0, 0};      // its LDS, with the table in memory and in LDS
+    bool tail_on[2] = {false, false}; // some instance takes that form
     bool any_driven = false;
     int max_iter = 1, max_cycles = 1;
     int rows = 2;     // stencil rows per thread
@@ -476,12 +477,7 @@ size_t tail_floats(const Inst &d) {
 }
 
 // The sizes and tables of an instance's levels mg_tail - 1 .. as k_mg_tail
-// reads them (MgTab; empty for a hierarchy of one level).  At most four words
-// per node of the tail and 60 per level, so that table and values stay below
-// 120 KB of LDS: a level's axes add up to a third of its nodes and 4 at most
-// where it can be coarsened (some axis has 3 nodes or more), to half and 3 on
-// the coarsest (some axis has 2 or more), with 12 words per axis index there,
-// 8 here.
+// reads them (MgTab; empty for a hierarchy of one level).
 std::vector<int> tail_table(const InstHost &h) {
     const Inst &d = h.d;
     std::vector<int> t;
@@ -515,6 +511,29 @@ std::vector<int> tail_table(const InstHost &h) {
         memcpy(&t[(size_t)(l - l0) * MG_TAB_HEAD], &e, sizeof e);
     }
     return t;
+}
+
+// First level of the tail and its table: the coarsest level, and finer ones
+// while they fit by nodes and by LDS.  A coarsest level whose table alone is
+// too large (a long axis that cannot be halved) has it read from memory.
+void plan_tail(InstHost &h) {
+    Inst &d = h.d;
+    auto fits = [&] { return (h.mg_tab.size() + tail_floats(d)) * 4 <= (size_t)MG_TAIL_LDS; };
+    d.mg_tail = d.nlev - 1;
+    h.mg_tab = tail_table(h);
+    d.mg_tlds = fits();
+    for (long sum = d.lev[d.nlev - 1].N; d.mg_tail > 1 && d.mg_tlds;) {
+        sum += d.lev[d.mg_tail - 1].N;
+        if (sum > MG_TAIL_NODES) break;
+        --d.mg_tail;
+        std::vector<int> t = tail_table(h);
+        t.swap(h.mg_tab);
+        if (fits()) continue;
+        t.swap(h.mg_tab);
+        ++d.mg_tail;
+        break;
+    }
+    d.mg_words = (int)h.mg_tab.size();
 }
 
 size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
@@ -673,14 +692,7 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 L.tiles_z = cdiv(L.nz, L.chunk);
                 h.mg_blocks[l] = (int)(mtxy * L.tiles_z);
             }
-            // levels of k_mg_tail: the coarsest, and finer ones while they fit
-            d.mg_tail = d.nlev - 1;
-            for (long sum = d.lev[d.nlev - 1].N; d.mg_tail > 1; --d.mg_tail) {
-                sum += d.lev[d.mg_tail - 1].N;
-                if (sum > MG_TAIL_NODES) break;
-            }
-            h.mg_tab = tail_table(h);
-            d.mg_words = (int)h.mg_tab.size();
+            plan_tail(h);
             d.mg_tab = cv.take<int>(h.mg_tab.size());
             d.mu = d.lev[0].mu[0];
             d.f = d.lev[0].rhs;
@@ -821,6 +833,13 @@ const void *fft_inv_fn(const tdgl_ctx *c) {
     return c->fx_p2 ? (const void *)k_fft_inv<true, FFT_X_PTS, false> : (const void *)k_fft_inv<false, FFT_X_PTS, false>;
 }
 
+// The multigrid tail for the context's coarsest levels, with its tables in LDS
+// or in memory.
+auto tail_fn(const tdgl_ctx *c, int tl) -> decltype(&k_mg_tail<1, true>) {
+    if (c->co_nodes <= CO_THREADS) return tl ? k_mg_tail<1, true> : k_mg_tail<1, false>;
+    return tl ? k_mg_tail<4, true> : k_mg_tail<4, false>;
+}
+
 tdgl_status upload_tables(tdgl_ctx *ctx) {
     for (int i = 0; i < ctx->n; ++i) {
         InstHost &h = ctx->inst[i];
@@ -852,7 +871,9 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
             const Inst &d = h.d;
             ctx->co_nodes = std::max(ctx->co_nodes, (int)h.H.lev.back().N);
             ctx->mg_tail = std::max(ctx->mg_tail, d.mg_tail);
-            ctx->tail_lds = std::max(ctx->tail_lds, (d.mg_words + tail_floats(d)) * 4);
+            size_t &lds = ctx->tail_lds[d.mg_tlds];
+            lds = std::max(lds, ((d.mg_tlds ? d.mg_words : 0) + tail_floats(d)) * 4);
+            ctx->tail_on[d.mg_tlds] = true;
             ctx->tail_nodes = std::max(ctx->tail_nodes, d.lev[d.mg_tail].N);
         }
     // prefix tables
@@ -942,9 +963,10 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
         for (const void *fn : {(const void *)k_fft_zsolve<2>, (const void *)k_fft_zsolve<4>})
             HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ctx->fz_lds));
     }
-    for (const void *fn : {(const void *)k_mg_tail<1>, (const void *)k_mg_tail<4>})
-        if (ctx->tail_lds > 0)
-            HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ctx->tail_lds));
+    for (int tl = 0; tl < 2; ++tl)
+        if (ctx->tail_lds[tl] > 0)
+            HIPCHK(hipFuncSetAttribute((const void *)tail_fn(ctx, tl), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)ctx->tail_lds[tl]));
     HIPCHK(hipMemcpy(ctx->d_pref_st, ps.data(), (n + 1) * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_flat, pf.data(), (n + 1) * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->d_pref_mg, pm.data(), pm.size() * 4, hipMemcpyHostToDevice));
@@ -1194,10 +1216,8 @@ tdgl_status enqueue_vcycle(tdgl_ctx *c, int cyc) {
     {
         ProfScope ps(c, TDGL_K_MG_COARSE);
         const dim3 th(std::min(CO_THREADS, (std::max(c->co_nodes, c->tail_nodes) + 63) / 64 * 64));
-        if (c->co_nodes <= CO_THREADS)
-            hipLaunchKernelGGL(k_mg_tail<1>, dim3(n), th, c->tail_lds, s, c->d_inst, n, cyc, kOmega);
-        else
-            hipLaunchKernelGGL(k_mg_tail<4>, dim3(n), th, c->tail_lds, s, c->d_inst, n, cyc, kOmega);
+        for (int tl = 1; tl >= 0; --tl)
+            if (c->tail_on[tl]) hipLaunchKernelGGL(tail_fn(c, tl), dim3(n), th, c->tail_lds[tl], s, c->d_inst, n, cyc, kOmega);
     }
     for (int l = c->mg_tail - 1; l >= 0; --l) {
         ProfScope ps(c, l == 0 ? TDGL_K_MG_FINE : TDGL_K_MG_COARSE);

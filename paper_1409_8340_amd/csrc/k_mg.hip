@@ -524,23 +524,25 @@ __device__ __forceinline__ const float *mg_coarsest(const MGLevel &L, const floa
 // takes 5 to 7 us, whatever its size; here an operation takes one barrier.
 // The levels' tables come to LDS in one piece, since a chain of pointer, table
 // and value loads costs an operation as much as a launch does.
-// A hierarchy of one level (tiny grids) is solved directly: its right side is
+// (TL false, for an instance whose coarsest level's table is larger than LDS:
+// read where it is.)  A hierarchy of one level (tiny grids) is solved directly: its right side is
 // f minus its weighted mean and the iterate starts from the stored mu.
 // 192 x 101 x 33 nodes (tail 24 x 14 x 5 and 12 x 8 x 3), per V-cycle: 78 us,
 // nearly all of it the coarsest level's sweeps, for seven launches of 125 us;
 // a run of six steps 11.6 -> 10.2 ms.
-template <int NPT>
+template <int NPT, bool TL>
 __global__ __launch_bounds__(CO_THREADS) void k_mg_tail(const Inst *__restrict__ insts, int ninst, int cyc,
                                                         float omega) {
     extern __shared__ float tail_sm[];
     const Inst &I = insts[blockIdx.x];
-    if (!I.driven || I.fft || mg_done(I, cyc)) return;
+    if (!I.driven || I.fft || TL != (I.mg_tlds != 0) || mg_done(I, cyc)) return;
     const int last = I.nlev - 1, lt = I.mg_tail, nt = (int)blockDim.x;
     // the levels' sizes and tables, from level lt - 1 on (see MgTab), then 3 N
     // floats per level: its iterates and right side
-    int *tab = (int *)tail_sm;
-    for (int i = threadIdx.x; i < I.mg_words; i += nt) tab[i] = I.mg_tab[i];
-    const float *ftab = (const float *)tail_sm;
+    const int *tab = TL ? (const int *)tail_sm : I.mg_tab;
+    if (TL)
+        for (int i = threadIdx.x; i < I.mg_words; i += nt) ((int *)tail_sm)[i] = I.mg_tab[i];
+    const float *ftab = (const float *)tab;
     auto lev = [&](int l) {
         MgTab v;
         const int *h = tab + (l - lt + 1) * MG_TAB_HEAD;
@@ -654,7 +656,7 @@ __global__ __launch_bounds__(CO_THREADS) void k_mg_tail(const Inst *__restrict__
     }
     // down
     __syncthreads();
-    float *base = tail_sm + I.mg_words;
+    float *base = tail_sm + (TL ? I.mg_words : 0);
     {
         const MgTab C = lev(lt);
         restrict_to(lev(lt - 1), C, I.lev[lt - 1].r, base + 2 * C.N, base);
@@ -696,8 +698,10 @@ __global__ __launch_bounds__(CO_THREADS) void k_mg_tail(const Inst *__restrict__
     const MGLevel &L = I.lev[lt];
     for (int m = threadIdx.x; m < L.N; m += nt) L.mu[0][m] = e[m];
 }
-template __global__ void k_mg_tail<1>(const Inst *, int, int, float);
-template __global__ void k_mg_tail<4>(const Inst *, int, int, float);
+template __global__ void k_mg_tail<1, true>(const Inst *, int, int, float);
+template __global__ void k_mg_tail<4, true>(const Inst *, int, int, float);
+template __global__ void k_mg_tail<1, false>(const Inst *, int, int, float);
+template __global__ void k_mg_tail<4, false>(const Inst *, int, int, float);
 
 // End of a Poisson solve: number of cycles and final residual; clears the
 // cycle words.  One thread per instance.

@@ -16,6 +16,11 @@ constexpr int CO_THREADS = 1024;
 // the tail at 12 x 8 x 3 alone / from 24 x 14 x 5 (1968 nodes) / from 48 x 26 x
 // 9 (13200): 11.9 / 11.5 / 14.3 ms.
 constexpr int MG_TAIL_NODES = 4096;
+// ... and most bytes of LDS for those levels' values and tables: what a CU's
+// 160 KB leave beside the static arrays (33 KB with four nodes per thread).
+// A level's table grows with the sum of its axes, not with its nodes, so on
+// thin grids this ends the tail sooner: 4096 x 1 x 1 starts it at 1024 nodes.
+constexpr int MG_TAIL_LDS = 127 * 1024;
 constexpr int FIN_THREADS = 256;  // threads per instance of the solve finalizers
 
 template <int R, bool NT, bool YZ>
@@ -74,7 +79,7 @@ __host__ __device__ constexpr int mgb_threads(int h) {
 }
 template <bool PRO, int S, bool RES>
 __global__ void k_mg_blk(const Inst *insts, const int *prefix, int ninst, int lv, int isrc, int cyc, float omega);
-template <int NPT>
+template <int NPT, bool TL>
 __global__ void k_mg_tail(const Inst *insts, int ninst, int cyc, float omega);
 __global__ void k_mg_finalize(const Inst *insts, int ninst, int count_step);
 __global__ void k_mu_mean_partial(const Inst *insts, const int *prefix, int ninst, int which);

@@ -167,6 +167,7 @@ struct Inst {
     int nlev;
     int mg_tail;         // coarsest levels from here on in one work-group (k_mg_tail)
     int mg_words;        // words of their table, from level mg_tail - 1 on
+    int mg_tlds;         // the tail copies it to LDS
     const int *mg_tab;
     MGLevel lev[kMaxLevels];
     // direct spectral Poisson solve (periodic x and y, open z)
