@@ -104,7 +104,7 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     gf1 *__restrict__ fw = (gf1 *)I.f;
 
     const float cx = I.cx, cy = I.cy, cz = I.cz;
-    float2 ux[ROWS], uz[ROWS];
+    float2 uxv[ROWS], uzv[ROWS], ux[ROWS], uz[ROWS];
     bool vy[ROWS];
     int off[ROWS], mode[ROWS];  // cell_src() of the thread's nodes; px and fac follow from x and ux
     bool all_plain = true;
@@ -112,12 +112,12 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     for (int r = 0; r < ROWS; ++r) {
         const int y = y0 + w * ROWS + r;
         vy[r] = (x < nx) && (y < ny);
-        ux[r] = to_scalar((y < ny) ? I.ux[y] : make_float2(1.f, 0.f));
-        uz[r] = to_scalar((y < ny) ? I.uz[y] : make_float2(1.f, 0.f));
+        uxv[r] = I.ux[min(y, ny - 1)];
+        uzv[r] = I.uz[min(y, ny - 1)];
         const CellSrc o = cell_src(I, x, y);
         off[r] = o.off;
         mode[r] = o.mode;
-        all_plain = all_plain && o.mode == SRC_PLAIN;
+        all_plain = all_plain && (o.mode == SRC_PLAIN || x > nx || y > ny);
     }
     const bool hthr = threadIdx.x < HALOv;
     int hgx = 0, hgy = 0, hlx = 0, hly = 0;
@@ -126,7 +126,8 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
         halo_cell<TYv>(threadIdx.x, x0, y0, hgx, hgy, hlx, hly);
         hs = cell_src(I, hgx, hgy);
     }
-    all_plain = __ballot(!all_plain) == 0 && __ballot(hthr && hs.mode != SRC_PLAIN) == 0;
+    all_plain = __ballot(!all_plain) == 0;
+    const bool halo_plain = __ballot(hthr && hs.mode != SRC_PLAIN && hgx <= nx && hgy <= ny) == 0;
     const bool zper = I.per[2] != 0;
     // plane behind v, -1: none (v one plane outside the grid at most)
     auto zpl = [&](int v) -> int { return (unsigned)v < (unsigned)nz ? v : (zper ? (v < 0 ? nz - 1 : 0) : -1); };
@@ -137,13 +138,21 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
     // load.  A plane's base address is scalar, the offsets in it stay the same.
     // The waves of a mid-size grid wait for memory most of their lives, so
     // what counts is how many are resident: with the row links scalar too, a
-    // sweep of two rows per thread needs 79 registers where it took 86 (6
-    // waves per SIMD, 5 before), one of four 120 where it took 140 (4, 3).
-    // Two and three planes ahead cost more waves than they hide.  Per step,
-    // one / two / three planes ahead, and before: 24 instances to 128 x 96 x
-    // 48 nodes, sweeps 801 / 847 / 853, 1015 us; 384 x 240 x 48 with a yz
-    // field 348 / 375 / 392, 372 us; assemble at 1024 x 1024 x 128 1108 us,
-    // 1241 before.
+    // sweep of two rows per thread needs 74 registers where it took 86 (6
+    // waves per SIMD, 5 before), one of four 108 where it took 140 (4, 3), the
+    // assemble 76 where it took 86.  Two and three planes ahead cost more
+    // waves than they hide (sweeps of 24 instances to 128 x 128 x 32 nodes 801
+    // us a step with one, 847 and 853 with two and three).
+    // A run of one or two planes (films, boxes below a million nodes) hides
+    // nothing, so there a sweep is its chain of latencies, and what is not
+    // needed shows: the scalar copies of the links are made once the planes'
+    // loads are on their way, rows of slots off the grid stand under a mask,
+    // the halo's boundary rules are not the own slots', and a lone plane loads
+    // no neighbours.  us per sweep with branches around the loads / without
+    // these four / now: 4096 x 4096 x 1 158 / 180 / 147, 1024 x 1024 x 1 13.1 /
+    // 15.5 / 13.5, 96 x 96 x 96 12.7 / 14.4 / 13.2, 200 x 150 x 60 18.8 / 18.8
+    // / 18.1, 320 x 320 x 128 98 / 95 / 95; assemble of 4096 x 4096 x 1 222 /
+    // 230 / 179, 320 x 320 x 128 143 / 138 / 124, 384 x 240 x 48 35 / 42 / 36.
     const unsigned hoff = (unsigned)hs.off;
     auto load_psi = [&](int v, bool need, float2 *f) {
         const int p = need ? zpl(v) : -1;
@@ -197,15 +206,26 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
         float2 fm[ROWS], fc[ROWS], hc;
         load_psi(k0, true, fc);
         load_halo(k0, true, hc);
-        load_psi(k0 - 1, true, fm);
-        load_psi(k0 + 1, true, f);
-        load_halo(k0 + 1, k0 + 1 < k1, h);
+        if (nz > 1) {
+            load_psi(k0 - 1, true, fm);
+            load_psi(k0 + 1, true, f);
+            load_halo(k0 + 1, k0 + 1 < k1, h);
+        } else {
+            h = hc;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) fm[r] = f[r] = fc[r];
+        }
         load_streams(k0, true, bh, dh, ep, mu);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            ux[r] = to_scalar(uxv[r]);
+            uz[r] = to_scalar(uzv[r]);
+        }
         settle_own(k0, fc, pc);
         settle_own(k0 - 1, fm, pm);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) lds[0][1 + w * ROWS + r][1 + lane] = pc[r];
-        if (hthr) lds[0][hly][hlx] = settle<YZ>(Pt, k0, nx, hs, hc, I.wz);
+        if (hthr) lds[0][hly][hlx] = halo_plain ? hc : settle<YZ>(Pt, k0, nx, hs, hc, I.wz);
     }
     const float mu_mean = (is_first_mode(MODE) && I.driven) ? (float)st->mu_mean : 0.f;
     const float ht2 = I.ht2, S2 = I.S2, u = I.u;
@@ -233,7 +253,7 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
         if (k + 1 < k1) {
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) lds[buf ^ 1][1 + w * ROWS + r][1 + lane] = pn[r];
-            if (hthr) lds[buf ^ 1][hly][hlx] = all_plain ? h : settle<YZ>(Pt, k + 1, nx, hs, h, I.wz);
+            if (hthr) lds[buf ^ 1][hly][hlx] = halo_plain ? h : settle<YZ>(Pt, k + 1, nx, hs, h, I.wz);
         }
         load_psi(k + 2, k + 2 <= k1, f);
         load_halo(k + 2, k + 2 < k1, h);
@@ -273,8 +293,8 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
                 const float2 xm = lds[buf][ly][lane], xp = lds[buf][ly][lane + 2];
                 const float2 ym = lds[buf][ly - 1][lane + 1], yp = lds[buf][ly + 1][lane + 1];
                 const unsigned m = (unsigned)off[r];
+                if (!vy[r]) continue;
                 if (MODE == MODE_ENERGY) {
-                    if (!vy[r]) continue;
                     // forward edges only; an edge beyond an open face does not exist.
                     const float a2 = cabs2(c);
                     const int y = y0 + w * ROWS + r;
@@ -299,10 +319,8 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
                 if (MODE == MODE_RHS) {
                     // f = sum_a (1/h_a^2) Im[psi^* (U psi_+ + U^* psi_-)] = Im[psi^* NS]
                     const float fv = rhs_node(c, ns);
-                    if (vy[r]) {
-                        (fw + pbase)[m] = fv;
-                        acc += (double)fv * (double)node_w(I, x, y0 + w * ROWS + r, k);
-                    }
+                    (fw + pbase)[m] = fv;
+                    acc += (double)fv * (double)node_w(I, x, y0 + w * ROWS + r, k);
                     continue;
                 }
                 float2 nw;
@@ -313,29 +331,24 @@ __device__ __forceinline__ void stencil_tile(const Inst *__restrict__ insts, con
                         noise ? langevin2(I, (unsigned)k * NXY + m, nstep) : make_float2(0.f, 0.f);
                     assemble_node(c, ep[r], u * (I.driven ? mu[r] - mu_mean : 0.f), ns, S2, ht2, noise, zz, bhv, dhv,
                                   nw, r2);
-                    if (vy[r]) {
-                        if (NT) {
-                            st2nt(bhw + pbase, m, bhv);
-                            st2nt(dhw + pbase, m, dhv);
-                        } else {
-                            st2(bhw + pbase, m, bhv);
-                            st2(dhw + pbase, m, dhv);
-                        }
-                        // side copies for the two-sweep super-tiles (one 16-byte
-                        // global store each)
-                        if (eL >= 0) st4(I.edge, (unsigned)eL + 2u * r + eplane * k, bhv, dhv);
-                        if (eR >= 0) st4(I.edge, (unsigned)eR + 2u * r + eplane * k, bhv, dhv);
-                        rmaxb = rmax_bits(rmaxb, r2);
+                    if (NT) {
+                        st2nt(bhw + pbase, m, bhv);
+                        st2nt(dhw + pbase, m, dhv);
+                    } else {
+                        st2(bhw + pbase, m, bhv);
+                        st2(dhw + pbase, m, dhv);
                     }
+                    // side copies for the two-sweep super-tiles (one 16-byte
+                    // global store each)
+                    if (eL >= 0) st4(I.edge, (unsigned)eL + 2u * r + eplane * k, bhv, dhv);
+                    if (eR >= 0) st4(I.edge, (unsigned)eR + 2u * r + eplane * k, bhv, dhv);
+                    rmaxb = rmax_bits(rmaxb, r2);
                 } else {
                     nw = jacobi(bh[r], dh[r], ns);
-                    const unsigned rb = rmax_bits(rmaxb, resid2(nw, c, dh[r], ht2));
-                    rmaxb = vy[r] ? rb : rmaxb;
+                    rmaxb = rmax_bits(rmaxb, resid2(nw, c, dh[r], ht2));
                 }
-                if (vy[r]) {
-                    if (NT) st2nt(dst + pbase, m, nw);
-                    else st2(dst + pbase, m, nw);
-                }
+                if (NT) st2nt(dst + pbase, m, nw);
+                else st2(dst + pbase, m, nw);
             }
         };
         if (zm && zp) rows(std::true_type{});
