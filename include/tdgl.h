@@ -368,17 +368,19 @@ tdgl_status tdgl_step_graph(tdgl_ctx *ctx, int nsteps, int budget, tdgl_step_sta
 tdgl_status tdgl_poisson_solve(tdgl_ctx *ctx, const float *f, float *mu);
 
 /* Stencil tiling: work-groups of 64 x 4*rows grid columns marching through
- * z runs of `chunk` planes.  Contexts of up to 2^20 nodes, and films (nz = 1,
- * open z) of any size, make two (films: four) Jacobi iterates per launch from
- * blocks of the grid held on chip when the tiling asks for single sweeps
- * (fused = persistent = 0); rows and chunk then concern the other passes.
- * The results are the same bits. */
+ * z runs of `chunk` planes.  Small contexts make two (films, nz = 1 with open
+ * z: four) Jacobi iterates per launch from blocks of the grid held on chip when
+ * the tiling asks for single sweeps (fused = persistent = 0); rows and chunk
+ * then concern the other passes.  They do by default up to about 2^19 nodes, in
+ * solves that take more than one sweep; after tdgl_autotune (up to 2^20 nodes,
+ * and films of any size) where it measured blocks to be faster, which
+ * tdgl_set_tiling does not change.  The results are the same bits. */
 typedef struct tdgl_tiling {
     int rows;        /* rows of the tile per thread: 1, 2 or 4               */
     int chunk;       /* z planes per work-group (instance 0 for tdgl_autotune) */
     int streaming;   /* 1: non-temporal hints on the read-once streams of the
                         sweep and assemble passes (default: on when the
-                        context's sweep arrays exceed 256 MB)               */
+                        context's sweep arrays exceed 320 MB)               */
     int fused;       /* 1: Jacobi sweeps run two per pass over HBM (the
                         second iterate on the tile from the first on the tile
                         and its one-node ring); results are bit-identical */

@@ -384,12 +384,12 @@ struct tdgl_ctx {
     int *d_pref_sr = nullptr;  // ... and of the seam-ring pre-pass (seam2 instances)
     int *d_pref_r4 = nullptr;  // blocks of the four-row Poisson right-side pass
     int tot_b = 0, tot_i = 0, tot_sr = 0, tot_r4 = 0;
-    // block solves (k_blk): the shape's index in kBlkShapes for a context of
-    // this size (-1: too large), whether the tiling uses it, and the
-    // assemble's iterates in the current solve
+    // block solves (k_blk): the shape's index in kBlkShapes (-1: none), the
+    // assemble's iterates in the current solve, and whether solves use them
     int *d_pref_blk = nullptr;
     int tot_blk = 0, blk_shape = -1, blk_a = 1;
-    bool blk = false, blk_on = true;  // blk_on: the tiling does not rule them out
+    bool blk = false, blk_on = false;  // blk_on: the tiling takes them
+    bool blk_run = false;              // the solve at hand does
     int rhs_rows = 0;  // rows per thread of the Poisson right side (0: rows)
     int *d_np_st = nullptr, *d_np_flat = nullptr, *d_np_mg0 = nullptr;
     int *d_np_r4 = nullptr;  // per instance: blocks of the four-row right-side pass
@@ -775,16 +775,12 @@ tdgl_status check_ctx(tdgl_ctx *ctx, int inst) {
 
 int fill_grid(long n) { return (int)std::min<long>(std::max<long>(cdiv(n, 256), 1), 8192); }
 
-// Block shapes of k_blk and the one a context takes (-1: none).  Measured per
-// iteration in back-to-back launches, single sweeps first: 32 x 32 x 16
-// 5.0 -> 2.5 us and 72 x 60 x 10 5.2 -> 2.5 us on small blocks (3.4 us on
+// Block shapes of k_blk and the one that a context can take (-1: none).
+// Measured per iteration in back-to-back launches, single sweeps first: 32 x 32
+// x 16 5.0 -> 2.5 us and 72 x 60 x 10 5.2 -> 2.5 us on small blocks (3.4 us on
 // 32 x 8 x 4: too few for the chip); 64 x 64 x 64 5.3 -> 3.6 us (3.95 on
-// 16 x 8 x 2) and 128 x 128 x 32 6.0 -> 4.7 us (5.6); 300 x 180 x 50 18.8 ->
-// 19.8 us: there the halo's iterates cost more than the launches they save.
-// Films make four iterates a launch: 512 x 512 x 1 4.5 -> 1.8 us (2.5 us with
-// three, 2.8 with two), and their halo has no planes to recompute, so they
-// take blocks at any size.  tdgl_autotune measures the block launch against
-// the best other tiling.
+// 16 x 8 x 2) and 128 x 128 x 32 6.0 -> 4.7 us (5.6).  Films make four iterates
+// a launch: 512 x 512 x 1 4.5 -> 1.8 us (2.5 us with three, 2.8 with two).
 struct BlkShape {
     int bx, by, bz, S, hz;
 };
@@ -804,8 +800,28 @@ int blk_shape_for(const std::vector<InstHost> &inst) {
 }
 int blk_depth(const tdgl_ctx *c) { return kBlkShapes[c->blk_shape].S; }
 
-// Whether this context's Jacobi solves run as block launches: a single-sweep
-// tiling on a grid small enough, and no z-seam phase (which k_blk has not).
+// Whether a context takes blocks before tdgl_autotune has measured them: its
+// blocks hold up to 512 K nodes, a quarter of them real ones where they hold
+// more than 256 K.  A block's time does not depend on how full it is, and on a
+// chip full of blocks the halo's iterates cost more than the launches saved.
+// us a step of undriven steps of 7 sweeps (films 6), single sweeps -> blocks:
+// 64 x 64 x 64 65 -> 56, 128 x 128 x 32 70 -> 68, 72 x 72 x 72 77 -> 66; beyond
+// the line 100 x 80 x 80 76 -> 90, 128 x 128 x 64 82 -> 98 and 4 x 64 x 64 x 64
+// 84 -> 102 (replayed); films 512 x 512 52 -> 43, 1280 x 1280 driven 245 ->
+// 266; blocks filled to a quarter or less: 30000 x 1 x 1 23 -> 37, a film of
+// 512 x 300 beside two boxes 85 -> 105, but 20 x 5000 x 1 56 -> 42.
+constexpr long long kBlkHeld = 512ll << 10, kBlkSparse = 256ll << 10;
+bool blk_default(const tdgl_ctx *c) {
+    if (c->blk_shape < 0) return false;
+    const BlkShape b = kBlkShapes[c->blk_shape];
+    const long long held = (long long)c->tot_blk * b.bx * b.by * b.bz;
+    long long nodes = 0;
+    for (const auto &h : c->inst) nodes += h.d.N;
+    return held <= kBlkHeld && (held <= kBlkSparse || 4 * nodes >= held);
+}
+
+// Whether this context's Jacobi solves can run as block launches: a
+// single-sweep tiling that takes them, and no z-seam phase (which k_blk has not).
 void update_blk(tdgl_ctx *c) { c->blk = c->blk_on && c->blk_shape >= 0 && !c->fused && !c->persist && !c->any_zseam; }
 
 // Forward (rows from src; SRC_PSI with the fused y and z pass only) and
@@ -933,6 +949,7 @@ tdgl_status upload_tables(tdgl_ctx *ctx) {
             HIPCHK(hipMemcpy(ctx->d_pref_blk, pb.data(), (n + 1) * 4, hipMemcpyHostToDevice));
             ctx->tot_blk = pb[n];
         }
+        ctx->blk_on = blk_default(ctx);
         update_blk(ctx);
     }
     ctx->tot_st = ps[n];
@@ -1172,7 +1189,7 @@ void launch_blk(tdgl_ctx *c, int l, int ns, int np, int pass) {
 
 // The assemble pass, with the Langevin draws where some instance has them.
 void launch_assemble(tdgl_ctx *c, int l = 0) {
-    if (c->blk) {
+    if (c->blk_run) {
         if (c->noisy) launch_blk<MODE_FIRSTN>(c, l, c->blk_a, 0, 0);
         else launch_blk<MODE_FIRST>(c, l, c->blk_a, 0, 0);
         return;
@@ -1291,6 +1308,25 @@ int pick_schedule(tdgl_ctx *ctx, int kind) {
     return c2 < c1 ? 2 : 1;
 }
 
+// Whether the next solve of kind `kind` runs as block launches: not where
+// the recent ones took one sweep, as those of a state at rest do.  Then there is
+// no launch to save, and the halo and the larger work-groups cost (512 x 512 x
+// 1 26 -> 31 us a step, 1280 x 1280 x 1 33 -> 77); the small blocks' are lighter
+// than a stencil tile all the same (48 x 48 x 48 31 -> 27, 17 x 17 x 17 30 -> 22).
+bool blk_now(tdgl_ctx *ctx, int kind) {
+    const std::vector<int> &h = ctx->sweep_hist[kind];
+    if (!ctx->blk || ctx->blk_shape == 0 || (int)h.size() != ctx->n * kHist) return ctx->blk;
+    double nodes = 0.0, sweeps = 0.0;
+    for (int i = 0; i < ctx->n; ++i)
+        for (int q = 0; q < kHist; ++q) {
+            const int sw = h[(size_t)i * kHist + q];
+            if (sw <= 0) return true;  // none yet, or a capped solve
+            nodes += ctx->inst[i].d.N;
+            sweeps += (double)ctx->inst[i].d.N * sw;
+        }
+    return sweeps >= 1.5 * nodes;
+}
+
 // Iterates the assemble of a block solve makes (1 .. S) so that solves of the
 // recent sweep counts end on a launch's last iterate with the fewest
 // launches, corrective ones included (S without history).
@@ -1362,7 +1398,7 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
     // hands over the rows below starts[k] not handed over before
     std::vector<int> starts{0};
     starts.reserve(MI + 1);
-    int remaining = n, launched = ctx->blk ? ctx->blk_a : 1, polled = 0;
+    int remaining = n, launched = ctx->blk_run ? ctx->blk_a : 1, polled = 0;
     // two-sweep passes from l = 1 (schedule 1) or after one single sweep
     // from l = 2 (schedule 2), whichever the recent sweep counts favour
     const int kind = count_step ? 0 : 1;
@@ -1398,10 +1434,10 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
         if (remaining == 0 || launched >= MI) break;
         const int l = launched;
         const bool pair = ctx->fused && !(sched == 2 && l == 1);
-        const int nr = std::min(ctx->blk ? blk_depth(ctx) : (pair ? 2 : 1), MI - l);
+        const int nr = std::min(ctx->blk_run ? blk_depth(ctx) : (pair ? 2 : 1), MI - l);
         {
             ProfScope ps(ctx, TDGL_K_SWEEP);
-            if (ctx->blk) launch_blk<MODE_SWEEP>(ctx, l, nr, l - starts.back(), (int)starts.size());
+            if (ctx->blk_run) launch_blk<MODE_SWEEP>(ctx, l, nr, l - starts.back(), (int)starts.size());
             else if (pair) launch_sweep2(ctx, l);
             else launch_stencil<MODE_SWEEP>(ctx, l);
         }
@@ -1415,11 +1451,11 @@ tdgl_status jacobi_loop(tdgl_ctx *ctx, tdgl_step_stats *acc, bool *strict_fail, 
     {
         ProfScope ps(ctx, TDGL_K_OTHER);
         hipLaunchKernelGGL(k_solve_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, count_step,
-                           launched, ctx->blk ? kBlkCode * blk_depth(ctx) + ctx->blk_a : sched, fin, ctx->pub_seq);
+                           launched, ctx->blk_run ? kBlkCode * blk_depth(ctx) + ctx->blk_a : sched, fin, ctx->pub_seq);
         // corrective sweep where needed (of a block solve: where the host
         // cannot rule it out)
         if (ctx->fused) launch_stencil<MODE_SWEEP>(ctx, -2);
-        if (ctx->blk) {
+        if (ctx->blk_run) {
             bool fix = false;
             for (int i = 0; i < n; ++i) {
                 const BlkPos b = blk_pos(ctx->blk_a, blk_depth(ctx), launched, conv_at[i] + 1);
@@ -1660,7 +1696,10 @@ tdgl_status enqueue_step_fixed(tdgl_ctx *ctx, int budget, bool exact = false) {
     const int n = ctx->n;
     hipStream_t s = ctx->stream;
     int code = ctx->fused ? 1 : 0;
-    if (ctx->blk) {
+    // (with up to three sweeps blocks save no launch, their corrective one
+    // included)
+    ctx->blk_run = ctx->blk && budget > (exact ? 1 : 3);
+    if (ctx->blk_run) {
         // exact: the solve is known to take `budget` sweeps
         const int S = blk_depth(ctx);
         ctx->blk_a = exact ? (budget - 1) % S + 1 : std::min(S, budget);
@@ -1681,7 +1720,7 @@ tdgl_status enqueue_step_fixed(tdgl_ctx *ctx, int budget, bool exact = false) {
     hipLaunchKernelGGL(k_solve_finalize, dim3(n), dim3(FIN_THREADS), 0, s, ctx->d_inst, n, 1, budget, code, nullptr,
                        0u);
     if (ctx->fused) launch_stencil<MODE_SWEEP>(ctx, -2);
-    if (ctx->blk && !exact) launch_blk<MODE_SWEEP>(ctx, -2, 0, 0, 0);
+    if (ctx->blk_run && !exact) launch_blk<MODE_SWEEP>(ctx, -2, 0, 0, 0);
     LAUNCHCHK();
     if (!ctx->any_driven) return TDGL_OK;
     hipLaunchKernelGGL(k_jav_partial, dim3(ctx->tot_flat), dim3(256), 0, s, ctx->d_inst, ctx->d_pref_flat, n);
@@ -2158,7 +2197,8 @@ tdgl_status tdgl_step(tdgl_ctx *ctx, int nsteps, tdgl_step_stats *stats) {
     }
     for (int step = 0; step < nsteps; ++step) {
         // ---- Jacobi solve (all instances) --------------------------------
-        if (ctx->blk) ctx->blk_a = pick_blk_a(ctx, 0);
+        ctx->blk_run = blk_now(ctx, 0);
+        if (ctx->blk_run) ctx->blk_a = pick_blk_a(ctx, 0);
         {
             ProfScope ps(ctx, TDGL_K_ASSEMBLE);
             launch_assemble(ctx);
@@ -2380,7 +2420,7 @@ struct Tiling {
     int persist = 0;  // one cooperative launch per Jacobi solve
     int rhs4 = 0;     // Poisson right side on 64 x 16 tiles (four rows per thread)
     int tys = 0;      // rows of the two-sweep super-tiles (0: tys_default(rows))
-    int blk = 1;      // block solves in place of single sweeps, where the context has a block shape
+    int blk = -1;     // block solves in place of single sweeps (-1: as the context has it)
 };
 
 tdgl_status apply_tiling(tdgl_ctx *ctx, const Tiling &t) {
@@ -2390,7 +2430,8 @@ tdgl_status apply_tiling(tdgl_ctx *ctx, const Tiling &t) {
     ctx->nt = t.nt != 0;
     ctx->fused = t.fused != 0 && !ctx->any_zseam;  // the two-sweep kernels have no z-seam phase
     ctx->persist = t.persist != 0 && !ctx->fused && !ctx->any_yz;
-    ctx->blk_on = t.blk != 0;
+    if (t.blk >= 0) ctx->blk_on = t.blk != 0;
+    ctx->blk_run = false;
     update_blk(ctx);
     for (auto &h : ctx->inst) set_tiling(h, t.rows, t.chunk, t.chunk2, t.tys);
     return upload_tiling(ctx);
@@ -2420,7 +2461,7 @@ bool tune_file_lookup(const char *path, const std::string &key, Tiling *t, doubl
     bool found = false;
     while (fgets(line, sizeof line, f)) {
         char k[4000];
-        int r, c, nt, fu, pe, c2 = 0, r4 = 0, ty = 0, bk = 1;
+        int r, c, nt, fu, pe, c2 = 0, r4 = 0, ty = 0, bk = 0;
         double u;
         // key rows chunk streaming fused persistent us [chunk2 [rhs4 [super-tile rows [blocks]]]]
         const int got =
@@ -2433,7 +2474,7 @@ bool tune_file_lookup(const char *path, const std::string &key, Tiling *t, doubl
             t->chunk2 = got >= 8 ? c2 : 0;
             t->rhs4 = got >= 9 ? r4 : 0;
             t->tys = got >= 10 ? ty : 0;
-            t->blk = got >= 11 ? (bk != 0) : 1;
+            t->blk = got >= 11 ? (bk != 0) : 0;  // (older lines: measured without)
             t->nt = nt;
             t->fused = fu;
             t->persist = pe;
@@ -2553,10 +2594,10 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
             if (us < best_us) {
                 best_us = us;
                 best = best_single;
-            } else if (!best.fused) {
-                best.blk = 0;
             }
+            best.blk = us < best_single_us;
         }
+        if (best.blk < 0) best.blk = ctx->blk_on;
         // two-sweep passes: the stencil passes that remain (the assemble
         // every step, the Poisson right side, an occasional single sweep)
         // take the z run under which the assemble is fastest
@@ -2781,6 +2822,7 @@ tdgl_status adjoint_step(tdgl_ctx *c, const AdjLayout &L, int iprev, int inext, 
     hipLaunchKernelGGL(k_adj_assemble, dim3(G), dim3(256), 0, s, c->d_inst, L.psibar, psim, mum, newest, older,
                        k >= 2 ? 1 : 0, L.part, L.adj);
     LAUNCHCHK();
+    c->blk_run = blk_now(c, 1);
     c->blk_a = 1;  // k_adj_assemble's warm start stands for iterate 1
     e = jacobi_loop(c, nullptr, nullptr, 0);
     if (e) return e;
