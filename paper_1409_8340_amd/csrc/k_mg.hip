@@ -294,7 +294,7 @@ __global__ __launch_bounds__(mgb_threads(S + RES)) void k_mg_blk(const Inst *__r
             v[q] += e;
         }
     }
-    const bool done = mg_done(I, cyc);
+    if (__ballot(mg_done(I, cyc)) != 0) return;  // (one answer for all)
 #pragma unroll
     for (int q = 0; q < NP; ++q) buf[0][q][t] = v[q];
     // z neighbours of plane q: the plane itself beyond an open face
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(mgb_threads(S + RES)) void k_mg_blk(const Inst *__r
         }
     }
     const int k1 = min(MGB_Z, nz - k0);
-    if (in && !done) {
+    if (in) {
 #pragma unroll
         for (int q = 0; q < MGB_Z; ++q)
             if (q < k1) dst[(k0 + q) * nxy + col] = v[H + q];
@@ -339,13 +339,13 @@ __global__ __launch_bounds__(mgb_threads(S + RES)) void k_mg_blk(const Inst *__r
                                (double)apy * ((double)P[syp] - mc) + (double)amy * ((double)P[sym] - mc) +
                                (double)apz[q] * (mnext - mc) + (double)amz[q] * (mprev - mc);
             const double r = ((double)rh[q] - fmd) - Amu;
-            if (in && !done && c < k1) {
+            if (in && c < k1) {
                 L.r[(k0 + c) * nxy + col] = (float)r;
                 const float ra = (float)fabs(r);
                 rmax = (ra > rmax || ra != ra) ? ra : rmax;
             }
         }
-        if (lv == 0 && !done && cyc + 1 < I.mu_max_cycles)
+        if (lv == 0 && cyc + 1 < I.mu_max_cycles)
             wg_max_to<NT>(row_slot(I.mures, I.rstride, cyc + 1, blockIdx.x), rmax, red);
     }
 }
