@@ -371,10 +371,10 @@ tdgl_status tdgl_poisson_solve(tdgl_ctx *ctx, const float *f, float *mu);
  * z runs of `chunk` planes.  Small contexts make two (films, nz = 1 with open
  * z: four) Jacobi iterates per launch from blocks of the grid held on chip when
  * the tiling asks for single sweeps (fused = persistent = 0); rows and chunk
- * then concern the other passes.  They do by default up to about 2^19 nodes, in
- * solves that take more than one sweep; after tdgl_autotune (up to 2^20 nodes,
- * and films of any size) where it measured blocks to be faster, which
- * tdgl_set_tiling does not change.  The results are the same bits. */
+ * then concern the other passes.  They do so up to about 2^19 nodes, in solves
+ * that take more than one sweep, unless tdgl_autotune measured single sweeps to
+ * be faster, a choice that tdgl_set_tiling leaves as it is.  The results are
+ * the same bits. */
 typedef struct tdgl_tiling {
     int rows;        /* rows of the tile per thread: 1, 2 or 4               */
     int chunk;       /* z planes per work-group (instance 0 for tdgl_autotune) */

@@ -2577,8 +2577,11 @@ tdgl_status tdgl_autotune(tdgl_ctx *ctx, const char *cache_path, tdgl_tiling *ch
                     best_single = t;
                 }
             }
-        // block solves stand in for single sweeps on small grids
-        if (ctx->blk_shape >= 0 && !ctx->any_zseam) {
+        // block solves stand in for single sweeps on small grids (on others the
+        // launch timed here, full of iterates and without a corrective one,
+        // promises what a solve does not keep: 2048 x 2048 x 1 27.1 -> 20.4 us an
+        // iterate, 486 -> 577 us a step)
+        if (blk_default(ctx) && !ctx->any_zseam) {
             tdgl_status e = apply_tiling(ctx, best_single);
             if (e) return e;
             const int S = blk_depth(ctx), reps = 4;
