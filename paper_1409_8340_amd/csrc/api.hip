@@ -684,11 +684,6 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 L.tiles_x = cdiv(L.nx, MTX);
                 L.tiles_y = cdiv(L.ny, MTY);
                 L.chunk = auto_chunk(mtxy, L.nz, 0);
-                // a spectral instance uses its level-0 tiles only for the
-                // mean of mu: z runs of at least one batch of loads (eight
-                // planes), so that a batch of small instances does not
-                // become a swarm of work-groups that each sum two planes
-                if (l == 0 && fft_eligible(p)) L.chunk = std::min(L.nz, std::max(L.chunk, 8));
                 L.tiles_z = cdiv(L.nz, L.chunk);
                 h.mg_blocks[l] = (int)(mtxy * L.tiles_z);
             }
@@ -719,7 +714,7 @@ size_t layout(int n, const tdgl_params *params, char *base, tdgl_ctx *ctx) {
                 h.fy_blocks = d.fyz ? cdiv(P, d.fyz) : fft_y_plan(p.nx, p.ny, p.nz).blocks;
                 h.fz_blocks = p.nz <= FFT_ZSERIAL ? cdiv(p.ny * P, 256) : p.ny * cdiv(P, FFT_ZTK);
             }
-            part_cap = std::max(part_cap, std::max(h.mg_blocks[0], h.fx_blocks));
+            part_cap = std::max(part_cap, d.fft ? h.fx_blocks : h.mg_blocks[0]);
         }
         d.part = cv.take<double>(part_cap);
         d.part_cap = part_cap;
@@ -1788,11 +1783,7 @@ tdgl_status tdgl_create(int n, const tdgl_params *params, void *ws, size_t ws_by
         return fail(TDGL_EDEVICE, "cannot read the number of compute units");
     }
     layout(n, params, (char *)ws, c);
-    c->nlev_max = 0;
-    for (auto &h : c->inst) {
-        c->any_driven = c->any_driven || h.p.driven;
-        if (!h.d.fft) c->nlev_max = std::max(c->nlev_max, h.d.nlev);
-    }
+    for (auto &h : c->inst) c->any_driven = c->any_driven || h.p.driven;
     auto bail = [&](tdgl_status st) { tdgl_destroy(c); return st; };
     // sweeps of a few microseconds finish before the host has reacted to a
     // launch's start: keep one more launch queued for small contexts

@@ -12,11 +12,12 @@
 // along y, the z systems by Thomas' algorithm with precomputed pivots in
 // double precision (its two sweeps evaluated as prefix scans of affine maps
 // across a wavefront), inverse FFT along y, complex-to-real inverse along x.
-// In a time step the forward x pass computes the right side f = Im[psi^* NS
-// psi] from psi itself, and the inverse one sums the weighted mean of mu, so
-// neither is a pass of its own.  Where a few kx planes (all y and z) fit a
-// work-group's LDS, the y transforms and the z systems are one kernel
-// (k_fft_yz) on a half spectrum stored kx-major.  The (0, 0) system
+// The inverse x pass also sums the weighted mean of mu.  Where a few kx planes
+// (all y and z) fit a work-group's LDS, for every spectral instance of the
+// context, the y transforms and the z systems are one kernel (k_fft_yz) on a
+// half spectrum stored kx-major; if all of them have an even ny, the forward x
+// pass of a time step then makes the right side f = Im[psi^* NS psi] from psi
+// itself (otherwise k_stencil<MODE_RHS> does).  The (0, 0) system
 // is singular (the constant mode); its right side is projected onto the
 // range (zero weighted mean) and its solution shifted to zero weighted mean,
 // which fixes sum_m w_m mu_m = 0 for the whole grid.
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(FFT_X_THREADS) void k_fft_fwd(const Inst *__restric
     }
 }
 
-// The inverse (complex-to-real) along x into mu (or out_ext), with the
+// The inverse (complex-to-real) along x into mu, with the
 // work-group's FP64 partial of the weighted mean of mu (weights: the control
 // volumes; the sum of k_mu_mean_partial, which read mu back in a pass of its
 // own: 120 us at 1024 x 1024 x 128).
