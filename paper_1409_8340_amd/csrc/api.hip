@@ -513,26 +513,36 @@ std::vector<int> tail_table(const InstHost &h) {
     return t;
 }
 
-// First level of the tail and its table: the coarsest level, and finer ones
-// while they fit by nodes and by LDS.  A coarsest level whose table alone is
-// too large (a long axis that cannot be halved) has it read from memory.
+// Words of tail_table().
+size_t tail_words(const InstHost &h) {
+    const Inst &d = h.d;
+    if (d.nlev < 2) return 0;
+    auto axes = [&](int l) { return (size_t)(h.H.lev[l].n[0] + h.H.lev[l].n[1] + h.H.lev[l].n[2]); };
+    const int l0 = d.mg_tail - 1, last = d.nlev - 1;
+    size_t w = (size_t)(d.nlev - l0) * MG_TAB_HEAD;
+    for (int l = l0; l <= last; ++l) {
+        if (l > l0) w += axes(l) * (l < last ? 6 : 2);
+        if (l < last) w += axes(l + 1) * 6;
+    }
+    return w;
+}
+
+// First level of the tail: the coarsest, and finer ones while they fit by nodes
+// and by LDS.  A coarsest level whose table alone is too large (a long axis
+// that cannot be halved) has it read from memory.
 void plan_tail(InstHost &h) {
     Inst &d = h.d;
-    auto fits = [&] { return (h.mg_tab.size() + tail_floats(d)) * 4 <= (size_t)MG_TAIL_LDS; };
+    auto fits = [&] { return (tail_words(h) + tail_floats(d)) * 4 <= (size_t)MG_TAIL_LDS; };
     d.mg_tail = d.nlev - 1;
-    h.mg_tab = tail_table(h);
     d.mg_tlds = fits();
-    for (long sum = d.lev[d.nlev - 1].N; d.mg_tail > 1 && d.mg_tlds;) {
-        sum += d.lev[d.mg_tail - 1].N;
-        if (sum > MG_TAIL_NODES) break;
-        --d.mg_tail;
-        std::vector<int> t = tail_table(h);
-        t.swap(h.mg_tab);
-        if (fits()) continue;
-        t.swap(h.mg_tab);
+    long sum = d.lev[d.nlev - 1].N;
+    while (d.mg_tail > 1 && d.mg_tlds) {
+        sum += d.lev[--d.mg_tail].N;
+        if (sum <= MG_TAIL_NODES && fits()) continue;
         ++d.mg_tail;
         break;
     }
+    h.mg_tab = tail_table(h);
     d.mg_words = (int)h.mg_tab.size();
 }
 
