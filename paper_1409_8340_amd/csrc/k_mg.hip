@@ -60,7 +60,10 @@ __device__ __forceinline__ float mg_threshold(const Inst &I) {
 }
 __device__ __forceinline__ bool mg_done(const Inst &I, int c) {
     if (c >= I.mu_max_cycles) return true;
-    return row_max_wave(I.mures, I.rstride, c) < mg_threshold(I);
+    // (row c in the lower half-wave, row 0 in the upper)
+    const float m = row_max_half(I.mures, I.rstride, (threadIdx.x & 32) ? 0 : c);
+    const float r = __shfl(m, 0, 64), r0 = __shfl(m, 32, 64);
+    return r < fmaxf(I.mu_tol, I.mu_rtol * r0);
 }
 
 // Shared column context: coefficient values of the column and its x/y
