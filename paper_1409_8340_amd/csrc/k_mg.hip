@@ -221,10 +221,12 @@ __global__ __launch_bounds__(256) void k_mg_prolong(const Inst *__restrict__ ins
 // finest six.  A thread holds one (x, y) column of the block with a halo of one
 // node per sweep (and one for the residual), its planes in registers, the
 // block's planes in LDS; what a sweep gets wrong at the halo's rim moves in by
-// one node per sweep and never reaches the block.  Every load is issued before
-// the convergence rows are looked at, which only the stores wait for.  The
-// operations on a node and their order are those of one sweep, correction or
-// residual at a time, so are the bits.
+// one node per sweep and never reaches the block.  The convergence rows are
+// read behind the block's loads, and the work-groups of a cycle that has ended
+// stop there: they took 5 to 7 us a launch to compute what was not stored
+// (replayed steps of 256 x 101 x 33, which launch every cycle, 1944 -> 1606 us).
+// The operations on a node and their order are those of one sweep, correction
+// or residual at a time, so are the bits.
 // Below 192 x 101 x 33: correction and two sweeps of 96 x 51 x 17 and 48 x 26 x
 // 9 nodes 10 us each (15 as three launches), a sweep and the residual 6.5 (10);
 // of the finest level two sweeps 11 us (16), two and the residual 19 (25).  The
